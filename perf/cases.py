@@ -8,6 +8,7 @@ follows from the case alone and their order from the seed, so that a case's
 work does not depend on the seed. Tokens are unit-norm Gaussian vectors.
 """
 import math
+import random
 
 import torch
 
@@ -122,10 +123,12 @@ def _lengths(case):
     return x.round().clamp(8, 180).to(torch.int64)
 
 
-def _spread(lo, hi, n):
-    """n values spread evenly over [lo, hi], in a fixed mixed order."""
+def _spread(lo, hi, n, order):
+    """n values spread evenly over [lo, hi], in the fixed order that `order` names (so that
+    long queries and long candidate lists do not go together)."""
     v = [lo + (hi - lo) * (2 * i + 1) // (2 * n) for i in range(n)]
-    return [v[(5 * i + 2) % n] for i in range(n)] if math.gcd(5, n) == 1 else v
+    random.Random(order).shuffle(v)
+    return v
 
 
 def _offsets(lens):
@@ -169,13 +172,13 @@ def _tokens(n, dim, dtype, gen):
 
 def _queries(case, dim, seed):
     """FP32 query tokens, their offsets and the longest query."""
-    lens = _spread(case["nq_lo"], case["nq_hi"], case["n_q"])
+    lens = _spread(case["nq_lo"], case["nq_hi"], case["n_q"], "tokens")
     return (_unit(sum(lens), dim, _gen(seed, 1)), _offsets(torch.tensor(lens)), max(lens))
 
 
 def _candidates(case, seed):
     """Candidate ids of each query, drawn without replacement."""
-    sizes = _spread(case["c_lo"], case["c_hi"], case["n_q"])
+    sizes = _spread(case["c_lo"], case["c_hi"], case["n_q"], "candidates")
     g = _gen(seed, 2)
     ids = [torch.randperm(case["pool"], generator=g, device=DEV)[:n].to(torch.int32) for n in sizes]
     return _offsets(torch.tensor(sizes)), torch.cat(ids)
@@ -261,7 +264,7 @@ def work(case):
                     flops=n * d)
     dim, pool = _dim(case), case["pool"]
     tokens = int(_lengths(case).sum())
-    nq = _spread(case["nq_lo"], case["nq_hi"], case["n_q"])
+    nq = _spread(case["nq_lo"], case["nq_hi"], case["n_q"], "tokens")
     fixed = sum(nq) * dim * 4
     if "M" in case:
         row = case["M"]
@@ -273,7 +276,7 @@ def work(case):
         row = dim * {"f32": 4, "fp8": 1}.get(case["dtype"], 2) + (4 if case["dtype"] == "fp8" else 0)
     per_doc = tokens / pool
     if kind.endswith("rerank"):
-        sizes = _spread(case["c_lo"], case["c_hi"], case["n_q"])
+        sizes = _spread(case["c_lo"], case["c_hi"], case["n_q"], "candidates")
         miss = 1.0
         for c in sizes:
             miss *= 1 - c / pool
