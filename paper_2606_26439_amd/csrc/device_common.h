@@ -54,15 +54,17 @@ __device__ __forceinline__ float xor_shfl(float v, int m) { return __shfl_xor(v,
 // executes it. (A CPU test builds kernels using it to gfx950 assembly and
 // checks the wait states and that the max after each swap reads both
 // registers.)
-__device__ __forceinline__ float max_rows4(float v) {
+__device__ __forceinline__ float max_row_pairs(float v) {
   float a = v, b = v;
   asm volatile("s_nop 3\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
-  v = fmaxf(a, b);
-  a = v;
-  b = v;
+  return fmaxf(a, b);
+}
+__device__ __forceinline__ float max_half_waves(float v) {
+  float a = v, b = v;
   asm volatile("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
   return fmaxf(a, b);
 }
+__device__ __forceinline__ float max_rows4(float v) { return max_half_waves(max_row_pairs(v)); }
 
 // Sum over the four 16-lane rows by the same two swaps, left in every lane:
 // (v_r0 + v_r1) + (v_r2 + v_r3), the pairs and order of an xor butterfly
