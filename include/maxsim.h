@@ -225,7 +225,10 @@ maxsim_status maxsim_pq_score(const maxsim_csr* queries, const maxsim_pq_docs* d
  * token of the batch) in `workspace`; the fused scorer then reads each
  * token's id and packed residual once, gathers P[id_j, i], decodes the
  * residual in registers and adds q_i . r_j before the max over tokens and the
- * sum over query tokens. Decoded vectors are never written.
+ * sum over query tokens. Decoded vectors are never written. Where building
+ * the table would cost more than it saves (short candidate lists, d = 64) the
+ * scorer gathers C[id_j] instead, with the same bits; the workspace is asked
+ * for all the same.
  *   queries    F16, same dim, max_len <= 64. Each query owns
  *              W = 16 * nqb table columns, nqb = ceil(max_len / 16) rounded
  *              up to a power of two; n_centroids and n_queries * W must stay
@@ -351,13 +354,12 @@ maxsim_status maxsim_pq_autotune(const maxsim_csr* queries, const maxsim_pq_docs
                                  const char* cache_path, char* report, size_t report_len);
 
 /*
- * Residual scorer tuning: the fused residual kernel keeps a ring of document
- * tiles in flight (centroid ids loaded several tiles ahead of the table
- * gathers they address, which run ahead of the matrix work); this call times
- * each ring shape on the given problem (synchronises `stream`), keeps the
- * fastest for the key (nbits, dim, query blocks, candidates or not),
- * rewrites cache_path (if not NULL) with every tuned key and writes a
- * one-line JSON report. Workspace as for maxsim_residual_score.
+ * Residual scorer tuning: a launch is split over one or several workgroups
+ * per place on the device (finer splits even out queries and lists of
+ * different lengths, coarser ones set up less); this call times each split
+ * on the given problem (synchronises `stream`), keeps the fastest for the key
+ * (nbits, dim, query blocks, candidates or not), rewrites cache_path (if not
+ * NULL) with every tuned key and writes a one-line JSON report. Workspace as for maxsim_residual_score.
  */
 maxsim_status maxsim_residual_autotune(const maxsim_csr* queries,
                                        const maxsim_residual_docs* docs,

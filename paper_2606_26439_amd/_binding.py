@@ -445,7 +445,7 @@ def pq_autotune(q: Tokens, d: PQDocs, cand: Candidates = None, reps: int = 3,
 
 def residual_autotune(q: Tokens, d: ResidualDocs, cand: Candidates = None, reps: int = 5,
                       cache_path: str = None, stream=None) -> dict:
-    """Times the residual scorer's load-pipeline shapes on this problem and
+    """Times the residual scorer's splits over workgroups on this problem and
     keeps the fastest for its key."""
     n = _n_pairs(q, d.n_docs, cand)
     out = torch.empty(max(n, 1), dtype=torch.float32, device=d.offsets.device)

@@ -122,8 +122,8 @@ struct PqCfg {
 };
 std::map<PqKey, PqCfg> g_pq_tuned;
 
-// Residual scorer: load-pipeline variant per (nbits, dim, query blocks,
-// candidates or not).
+// Residual scorer: how finely a launch is split over workgroups (one of
+// RES_PIPES variants) per (nbits, dim, query blocks, candidates or not).
 struct ResKey {
   int nbits, dim, nqb, cand;
   bool operator<(const ResKey& o) const {
@@ -131,7 +131,7 @@ struct ResKey {
   }
 };
 struct ResCfg {
-  int pipe = -1;  // -1: automatic
+  int pipe = -1;  // variant (-1: automatic)
 };
 std::map<ResKey, ResCfg> g_res_tuned;
 
@@ -918,9 +918,29 @@ struct ResPlan {
   size_t ws = 0;
 };
 
-// Untuned keys: ids two tiles ahead of the table gathers, which run two tiles
-// ahead of the compute.
-constexpr int RES_DEFAULT_PIPE = 2;
+// Untuned keys: up to eight workgroups per place on the device.
+constexpr int RES_DEFAULT_PIPE = 3;
+
+// Whether the scorer gathers the centroids themselves (2 * dim bytes a token)
+// instead of rows of a centroid-query table (64 bytes a token and block of 16
+// query tokens) that has to be built first. Measured, the scorer takes about
+// 0.094 ps per gathered byte, and the table is built at 3.3 TB/s (centroids
+// read, table written) after a launch worth 13 MB at that rate, so in bytes of
+// the build: direct when 0.31 * tokens * (2 * dim - 64 * blocks) is below it.
+// On either side of the line, 2^17 centroids, one 32-token query, d = 128:
+// 3,000 candidates 21 us direct against 34 us, 30,000 candidates 96 against
+// 74 us. Both forms give the same bits.
+bool residual_direct(const ResParams& P, const maxsim_csr* q, const maxsim_residual_docs* d,
+                     const maxsim_candidates* cand) {
+  if (q->n_sets <= 0 || d->n_docs <= 0) return true;
+  const double per_doc = (double)d->n_tokens / (double)d->n_docs;
+  const double tokens = (cand ? (double)cand->n_total : (double)q->n_sets * (double)d->n_docs) * per_doc;
+  const double mean_len = (double)q->n_tokens / (double)q->n_sets;
+  const double blocks = std::min<double>(P.nqb, std::max(1.0, std::ceil(mean_len / 16)));
+  const double build =
+      13e6 + (double)d->n_centroids * (2.0 * d->dim + 4.0 * (double)P.n_cols);
+  return 0.31 * tokens * (2.0 * d->dim - 64.0 * blocks) < build;
+}
 
 maxsim_status plan_residual(const maxsim_csr* q, const maxsim_residual_docs* d,
                             const maxsim_candidates* cand, float* scores, ResPlan& pl,
@@ -978,19 +998,23 @@ maxsim_status plan_residual(const maxsim_csr* q, const maxsim_residual_docs* d,
   P.dim = d->dim;
   P.nbits = d->nbits;
   P.nqb = pow2_at_least(std::max(1, (q->max_len + 15) / 16));
-  // about eight resident workgroups per CU over the launch, chunks of at
-  // least 64 documents
+  // limits: below 2^31 work items of a query and at least 64 documents (about
+  // eight per CU over the batch), each spanning less than 2^31 documents or
+  // candidate positions; a wave of the scorer never spans more than an item
   const int64_t per_query = cand ? (q->n_sets > 0 ? cand->n_total / q->n_sets : 0) : d->n_docs;
   const int64_t want = (int64_t)device_info().cus * 8;
   const int64_t nq = std::max<int64_t>(1, q->n_sets);
   int64_t n_chunks = std::max<int64_t>(1, (want + nq - 1) / nq);
   n_chunks = std::min<int64_t>(n_chunks, std::max<int64_t>(1, per_query / 64));
   if (n_chunks * nq > 0x7fffffffLL) return fail(MAXSIM_EUNSUPPORTED, "residual: too many work items");
-  // a work item's span of documents (or candidate positions) stays in 32 bits
   const int64_t span_bound = (cand ? cand->n_total : d->n_docs) / n_chunks + 1;
   if (span_bound >= 0x7fffffffLL - 64)
     return fail(MAXSIM_EUNSUPPORTED, "residual: too many documents per work item");
-  P.n_chunks = (int)n_chunks;
+  P.cus = device_info().cus;
+  P.n_pairs = n_pairs;
+  // a wave's span of positions is counted in 32 bits: a pool near that size
+  // is shared out by documents, not by tokens
+  P.n_tokens = d->n_docs < 0x7fffffffLL - 64 ? d->n_tokens : 0;
   P.n_cols = q->n_sets * 16 * P.nqb;
   if (d->n_centroids >= (1 << 24) || P.n_cols >= (1 << 24) ||
       (uint64_t)d->n_centroids * (uint64_t)P.n_cols >= (1ull << 32))
@@ -1006,6 +1030,7 @@ maxsim_status plan_residual(const maxsim_csr* q, const maxsim_residual_docs* d,
     pipe = it == g_res_tuned.end() ? RES_DEFAULT_PIPE : it->second.pipe;
   }
   P.pipe = pipe;
+  P.direct = residual_direct(P, q, d, cand) ? 1 : 0;
   return MAXSIM_OK;
 }
 

@@ -167,3 +167,52 @@ __device__ __forceinline__ const char* zero_row_ptr() {
   asm volatile("" : "+s"(p));
   return (const char*)p;
 }
+
+// Loads from global memory straight into LDS, and the waits that go with
+// them. Lane l's B bytes (4 or 16) land at lds + l * B for the active lanes;
+// lds is wave-uniform.
+//
+// Written as assembly because the compiler's wait insertion takes any LDS read
+// that does not overlap a slot it can name as one that needs every such load
+// in flight to have landed (a wait for all vector memory operations), which
+// empties a ring of prefetched slots at each read of another table in LDS.
+// The instruction has no register result, so nothing of it is in the
+// register allocator's hands; the compiler only counts fewer operations in
+// flight than there are, which makes its own waits stricter, never looser.
+// The memory clobbers keep LDS accesses on their side of each load and wait.
+// The wave's own count is the caller's: lds_wait<N>() returns when at most N
+// vector memory operations of the wave are in flight (they retire in order).
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+template <int B, bool NT>
+__device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
+  static_assert(B == 4 || B == 16, "4 or 16 bytes per lane");
+  lds = __builtin_amdgcn_readfirstlane(lds);
+  if constexpr (B == 16 && NT)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
+                 :: "v"(src), "s"(lds) : "memory", "m0");
+  else if constexpr (B == 16)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(src), "s"(lds) : "memory", "m0");
+  else if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off nt"
+                 :: "v"(src), "s"(lds) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+                 :: "v"(src), "s"(lds) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void vmem_wait() {
+  static_assert(N >= 0 && N <= 63, "the counter has six bits");
+  if constexpr (N == 0) {
+    // visible to the compiler: its own loads need no further wait either
+    // (vmcnt in bits 3:0 and 15:14, the other counters at their maxima)
+    __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));
+    asm volatile("" ::: "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+  }
+}
+// every LDS access issued so far is complete
+__device__ __forceinline__ void lds_reads_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }

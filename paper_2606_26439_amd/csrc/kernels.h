@@ -153,12 +153,14 @@ struct ResParams {
   int32_t dim;    // 64, 128 or 256
   int32_t nbits;  // 1, 2 or 4
   int32_t nqb;    // 16-column query blocks (1, 2, 4)
-  int32_t n_chunks;  // document-range chunks per query
-  int32_t pipe;      // load-pipeline variant, 0 .. RES_PIPES - 1
-  int32_t pad;
+  int32_t pipe;   // split of the launch over workgroups, 0 .. RES_PIPES - 1
+  int32_t direct; // 1: the scorer gathers centroids and no table is built
+  int32_t cus;    // compute units of the device
+  int64_t n_pairs;   // scores: n_q * n_docs, or the candidate count
+  int64_t n_tokens;  // document tokens shared out to the waves (0: documents are)
 };
 constexpr int RES_PIPES = 4;
-// Builds the centroid-query table, then scores (grid n_q * n_chunks).
+// Builds the centroid-query table (unless direct), then scores.
 hipError_t launch_residual(const ResParams& P, hipStream_t s);
 
 // ---- top-k ----
