@@ -683,17 +683,25 @@ bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_can
                   int want_nqb, PqPlan& pl) {
   if (q->dtype != MAXSIM_F16 || d->cb_dtype != MAXSIM_F16) return false;
   if (d->dsub != 8 && d->dsub != 16 && d->dsub != 32) return false;
-  const size_t lds = (size_t)d->M * d->K * d->dsub * 2;
-  if (lds > device_info().max_lds) return false;
   if (!aligned(d->codebooks, 16) || (q->n_tokens > 0 && !aligned(q->tokens, 16))) return false;
   const int dim = d->M * d->dsub;
   const int bpq = pow2_at_least(std::max(1, (q->max_len + 15) / 16));
   if (bpq * dim > 1024) return false;  // query operand registers
+  if (pq_mfma_lds(d->M, d->K, d->dsub, std::min(8, 1024 / dim), 2) > device_info().max_lds)
+    return false;
+  // Query blocks per document pass. Eight at d <= 64 (0.50 ms against 0.62
+  // with four for 32 queries over 60K documents); four above: at d = 128 they
+  // leave four waves per SIMD (64 queries over 250K documents 7.24 against
+  // 7.43 ms with eight), at d = 256 two blocks decode too often (2.5 against
+  // 1.75 ms). No more queries than there are (one 10-token query over 20K
+  // documents: 24 us with one block, 53 with eight).
   int nqb = bpq;
   if (!cand) {
-    const int cap = want_nqb > 0 ? want_nqb : 8;
+    const int cap = want_nqb > 0 ? want_nqb : (dim <= 64 ? 8 : 4);
+    const int queries = (int)std::min<int64_t>(8, std::max<int64_t>(1, q->n_sets));
+    const int need = bpq * pow2_at_least(queries);
     nqb = 8;
-    while (nqb > bpq && (nqb > cap || nqb * dim > 1024)) nqb >>= 1;
+    while (nqb > bpq && (nqb > cap || nqb > need || nqb * dim > 1024)) nqb >>= 1;
   } else if (want_nqb > 0 && want_nqb != bpq) {
     return false;  // one query per group with candidate lists
   }
@@ -701,18 +709,21 @@ bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_can
   P.bpq = bpq;
   P.nqb = nqb;
   P.group = nqb / bpq;
-  P.nw = 8;
-  const int64_t n_groups = (q->n_sets + P.group - 1) / P.group;
+  // two waves where the codebooks leave no room for eight waves' rings
+  P.nw = pq_mfma_lds(d->M, d->K, d->dsub, nqb, 8) <= device_info().max_lds ? 8 : 2;
+  // (beyond 2^31 items of a query group and at least 64 documents, about eight
+  // per CU, the table kernel is asked)
+  const int64_t n_groups = std::max<int64_t>(1, (q->n_sets + P.group - 1) / P.group);
   const int64_t per_group_docs =
       cand ? (q->n_sets > 0 ? cand->n_total / q->n_sets : 0) : d->n_docs;
-  // about eight resident workgroups per CU over the whole launch, chunks of
-  // at least 64 documents
-  const int64_t want = (int64_t)device_info().cus * 8;
-  int64_t n_chunks = std::max<int64_t>(1, (want + n_groups - 1) / std::max<int64_t>(1, n_groups));
+  int64_t n_chunks = ((int64_t)device_info().cus * 8 + n_groups - 1) / n_groups;
   n_chunks = std::min<int64_t>(n_chunks, std::max<int64_t>(1, per_group_docs / 64));
-  if (n_chunks * std::max<int64_t>(1, n_groups) > 0x7fffffffLL) return false;
-  P.n_chunks = (int)n_chunks;
-  pl.lds = lds;
+  if (n_chunks * n_groups > 0x7fffffffLL) return false;
+  P.cus = device_info().cus;
+  // a wave's span of positions is counted in 32 bits: a pool near that size
+  // is shared out by documents, not by tokens
+  if (d->n_docs >= 0x7fffffffLL - 64) P.tokens_per_query = 0;
+  pl.lds = pq_mfma_lds(d->M, d->K, d->dsub, nqb, P.nw);
   pl.ws = 0;
   pl.variant = 1;
   return true;

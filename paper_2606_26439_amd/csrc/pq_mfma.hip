@@ -14,9 +14,21 @@
 // end two xor-shuffles finish the max over rows and four sum a query's
 // tokens. FP16 products are exact and accumulate in FP32.
 //
-// Work item = (doc chunk, group of queries). Without candidate lists a group
-// holds NQB / BPQ queries (BPQ = 16-column blocks per query, from the
-// query-length bound); with candidate lists a group is one query.
+// A work position is (query group, document), or a candidate; every wave takes
+// an equal share of them (document tokens, or candidates). Without candidate
+// lists a group holds NQB / BPQ queries (BPQ = 16-column blocks per query,
+// from the query-length bound); with candidate lists a group is one query,
+// scored with its own number of blocks. Codes arrive by direct-to-LDS loads
+// four tiles ahead, document offsets sit in lane registers, and scores are
+// written 64 documents at a time, so no step waits for an offset or a store.
+//
+// Bound: the matrix cores (2 * Nq * d per document token, 11% more on clamped
+// rows). 64 queries of 32 tokens over 250K documents: 7.24-7.51 ms, 1.21-1.26
+// PFLOP/s, the rate of a large FP16 matrix product on the same card (8.07 ms
+// with one wave per strided document, a scalar offset load at each document
+// and eight query blocks). Eight queries of 8 to 64 tokens with 1K to 100K
+// candidates, top-k included: 425 us; 701 when every query had the same number
+// of workgroups and the blocks of the longest query.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -42,49 +54,29 @@ struct PqCodes<16> {
   }
 };
 
-template <int M, int DSUB, int NQB, int NW>
-__global__ __launch_bounds__(NW * 64) void pq_mfma_kernel(PqParams P) {
-  extern __shared__ u32x4 cb_lds[];  // codebooks [M][K][DSUB] FP16
+constexpr int PF = PQ_RING;
+
+// One wave's scores: positions [lo, hi) (position base + b is document b, or
+// position p is candidate p) of the gsz queries from a0 on, whose tokens fill
+// NB blocks of 16 columns, bpq of them per query.
+template <int M, int DSUB, int NB>
+__device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int gsz, int bpq,
+                                            int64_t base, int64_t lo, int64_t hi,
+                                            const char* cbl, char* ring, float* sc,
+                                            const char* zrow) {
+  constexpr int SLOT = 16 * M;  // bytes of a ring slot
   constexpr int DIM = M * DSUB;
   constexpr int NKS = DIM / 32;  // k-steps of 32
   typedef typename PqCodes<M>::type cvec;
   const int lane = lane_id();
   const int r = lane & 15, g = lane >> 4;
-  const int wave = uniform(threadIdx.x >> 6);
   const int K = P.K;
-  const int bpq = P.bpq;            // 16-column blocks per query
-  const int gsz = P.group;          // queries per group
-  const int64_t n_groups = (P.n_q + gsz - 1) / gsz;
-
-  const int64_t item = blockIdx.x;
-  const int64_t grp = item % n_groups;
-  const int64_t chunk = item / n_groups;
-  const int64_t a0 = grp * gsz;
-
-  // doc (or candidate position) range of this item
-  int64_t p0, p1;
-  if (P.cand_off == nullptr) {
-    p0 = (P.n_docs * chunk) / P.n_chunks;
-    p1 = (P.n_docs * (chunk + 1)) / P.n_chunks;
-  } else {
-    const int64_t c0 = P.cand_off[a0], c1 = P.cand_off[a0 + 1];
-    p0 = c0 + ((c1 - c0) * chunk) / P.n_chunks;
-    p1 = c0 + ((c1 - c0) * (chunk + 1)) / P.n_chunks;
-  }
-  if (p0 >= p1) return;  // uniform for the whole workgroup
-
-  // ---- codebooks into LDS (16-byte copies) ----
-  {
-    const int n16 = M * K * DSUB * 2 / 16;
-    const u32x4* src = (const u32x4*)P.codebooks;
-    for (int e = threadIdx.x; e < n16; e += NW * 64) cb_lds[e] = src[e];
-  }
 
   // ---- query operand registers: block nb = query a0 + nb / bpq, rows
   // (nb % bpq) * 16 + r of that query (zero past its end) ----
-  f16x8 qb[NQB][NKS];
+  f16x8 qb[NB][NKS];
 #pragma unroll
-  for (int nb = 0; nb < NQB; ++nb) {
+  for (int nb = 0; nb < NB; ++nb) {
     const int64_t a = a0 + nb / bpq;
     int nq = 0;
     int64_t q0 = 0;
@@ -105,16 +97,18 @@ __global__ __launch_bounds__(NW * 64) void pq_mfma_kernel(PqParams P) {
   // per query of the group (bit gq): exists, has tokens, exceeds its bound
   uint32_t valid_m = 0, nonempty_m = 0, poison_m = 0;
 #pragma unroll
-  for (int gq = 0; gq < NQB; ++gq) {
+  for (int gq = 0; gq < NB; ++gq) {
     const int64_t a = a0 + gq;
     if (gq < gsz && a < P.n_q) {
       const int nq = (int)(P.q_off[a + 1] - P.q_off[a]);
       valid_m |= 1u << gq;
       if (nq > 0) nonempty_m |= 1u << gq;
-      if (nq > bpq * 16) poison_m |= 1u << gq;
+      if (nq > P.bpq * 16) poison_m |= 1u << gq;
     }
   }
-  __syncthreads();
+  valid_m = __builtin_amdgcn_readfirstlane(valid_m);
+  nonempty_m = __builtin_amdgcn_readfirstlane(nonempty_m);
+  poison_m = __builtin_amdgcn_readfirstlane(poison_m);
 
   // per-lane decode constants of k-step c: subspace m = (c*32 + g*8) / DSUB,
   // offset o inside the centroid; the 32/DSUB subspaces of one k-step lie in
@@ -127,83 +121,106 @@ __global__ __launch_bounds__(NW * 64) void pq_mfma_kernel(PqParams P) {
     lbase[c] = (m * K * DSUB + o) * 2;
     lsh[c] = 8 * (m & 3);
   }
-  const char* cbl = (const char*)cb_lds;
 
-  // ---- cursor over (document, 16-row tile) steps of this wave's documents
-  // p0 + wave, p0 + wave + NW, ...; offsets by scalar loads one doc ahead ----
+  // ---- cursor over (document, 16-row tile) steps of [lo, hi). The starts
+  // and lengths of 64 documents at a time sit in the lanes' registers, so a
+  // document change reads a lane instead of waiting for memory.
   const bool has_cand = P.cand_off != nullptr;
-  auto doc_of = [&](int64_t pp) -> int64_t {
-    return has_cand ? (int64_t)sload_i32(P.cand_ids, pp) : pp;
-  };
-  int64_t cp = p0 + wave;
-  int64_t ct0 = 0, nx_s = 0, nx_e = 0;
-  int cnd = 0, ctile = 0;
-  if (cp < p1) {
-    const int64_t b0 = doc_of(cp);
-    ct0 = sload_i64(P.d_off, b0);
-    cnd = (int)(sload_i64(P.d_off, b0 + 1) - ct0);
-    if (cp + NW < p1) {
-      const int64_t b1 = doc_of(cp + NW);
-      nx_s = sload_i64(P.d_off, b1);
-      nx_e = sload_i64(P.d_off, b1 + 1);
+  const int span = (int)(hi - lo);
+  int64_t m_start = 0;
+  int m_len = 0;
+  auto load_meta = [&](int first) {
+    m_start = 0;
+    m_len = 0;
+    if (first + lane < span) {
+      const int64_t p = lo + first + lane;
+      const int64_t b = has_cand ? (int64_t)P.cand_ids[p] : p - base;
+      m_start = P.d_off[b];
+      m_len = (int)(P.d_off[b + 1] - m_start);
     }
-  }
-  auto next_doc = [&]() {
-    cp += NW;
+    // waited for here, once in 64 documents, so no other path waits for it
+    vmem_wait<0>();
+  };
+  int cp = 0, ctile = 0, cnd = 0;
+  int64_t ct0 = 0;
+  auto enter_doc = [&]() {  // document cp becomes the cursor's
+    if ((cp & 63) == 0 && cp < span) load_meta(cp);
+    ct0 = readlane64(m_start, cp & 63);
+    cnd = __builtin_amdgcn_readlane(m_len, cp & 63);
     ctile = 0;
-    ct0 = nx_s;
-    cnd = (int)(nx_e - nx_s);
-    if (cp + NW < p1) {
-      const int64_t b1 = doc_of(cp + NW);
-      nx_s = sload_i64(P.d_off, b1);
-      nx_e = sload_i64(P.d_off, b1 + 1);
-    }
   };
+  enter_doc();
   constexpr int F_VALID = 1, F_EMPTY = 2, F_DLAST = 4;
-  const cvec* codes = (const cvec*)P.codes;
-  const cvec* const zero = (const cvec*)zero_row_ptr();
-  // every refill issues exactly one code load (a zero row when idle)
-  auto fill = [&](cvec& cv, int& fl, int64_t& pp) {
-    const cvec* src = zero;
-    int f = 0;
-    pp = cp;
-    if (cp < p1) {
+  // Codes come straight into a ring of PF tile slots in LDS (16 * M bytes
+  // each, four bytes per lane), so their loads hold no registers and nothing
+  // but this wave's own counted waits waits for them. Every refill issues one
+  // load (from the zero row when there is nothing left).
+  const uint32_t ring_at = lds_offset(ring);
+  const int crow = lane * 4 / M, ccol = lane * 4 % M;
+  auto refill = [&](int k) -> int {
+    const char* src = zrow;
+    int f = 0, lim = 0;
+    bool last = false;
+    if (cp < span) {
+      last = true;
       if (cnd == 0) {
         f = F_VALID | F_EMPTY;
       } else {
-        const int row = ctile * 16 + r;
-        src = codes + ct0 + (row < cnd ? row : cnd - 1);
-        f = F_VALID | ((ctile + 1) * 16 >= cnd ? F_DLAST : 0);
+        src = (const char*)P.codes + (ct0 + ctile * 16) * M;
+        lim = cnd - ctile * 16 - 1;
+        last = lim < 16;
+        f = F_VALID | (last ? F_DLAST : 0);
       }
     }
-    cv = *src;
-    fl = f;
-    if (cp < p1) {
-      if (cnd == 0 || (ctile + 1) * 16 >= cnd)
-        next_doc();
-      else
-        ++ctile;
+    if (4 * M >= 64 || lane < 4 * M)
+      load_to_lds<4, false>(src + (crow < lim ? crow : lim) * M + ccol, ring_at + k * SLOT);
+    if (last) {
+      ++cp;
+      enter_doc();
+    } else {
+      ++ctile;
+    }
+    return f;
+  };
+
+  // 64 documents' scores are kept in LDS, a row of 64 for the query whose last
+  // block is nb, and written a row at a time
+  float* const out = P.scores + lo + (has_cand ? 0 : (a0 - base / P.n_docs) * P.n_docs);
+  int n_out = 0;  // documents scored
+  auto put = [&](int nb, float v) {
+    if (lane == 0) sc[nb * 64 + (n_out & 63)] = v;
+  };
+  auto flush = [&](int n) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      if ((nb + 1) % bpq == 0) {
+        const int gq = nb / bpq;
+        if (((valid_m >> gq) & 1u) && lane < n) {
+          // query longer than its bound: NaN (as a bit pattern; this file
+          // assumes no NaN arithmetic)
+          const float v =
+              ((poison_m >> gq) & 1u) ? __builtin_bit_cast(float, 0x7fc00000u) : sc[nb * 64 + lane];
+          out[(int64_t)gq * P.n_docs + n_out - n + lane] = v;
+        }
+      }
     }
   };
-
-  auto store = [&](int64_t pp, int gq, float v) {
-    // query longer than its bound: NaN (as a bit pattern; this file assumes
-    // no NaN arithmetic)
-    if ((poison_m >> gq) & 1u) v = __builtin_bit_cast(float, 0x7fc00000u);
-    P.scores[has_cand ? pp : (a0 + gq) * P.n_docs + pp] = v;
+  auto scored = [&]() {
+    ++n_out;
+    if ((n_out & 63) == 0) flush(64);
   };
 
-  float mx[NQB];
+  float mx[NB];
 #pragma unroll
-  for (int nb = 0; nb < NQB; ++nb) mx[nb] = -__builtin_inff();
+  for (int nb = 0; nb < NB; ++nb) mx[nb] = -__builtin_inff();
 
-  auto consume = [&](const cvec& cv, int fl, int64_t pp) {
+  auto consume = [&](const cvec& cv, int fl) {
     if (!(fl & F_VALID)) return;
     if (fl & F_EMPTY) {
-      if (lane == 0) {
-        for (int gq = 0; gq < NQB; ++gq)
-          if ((valid_m >> gq) & 1u) store(pp, gq, ((nonempty_m >> gq) & 1u) ? -__builtin_inff() : 0.f);
-      }
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        put(nb, ((nonempty_m >> (nb / bpq)) & 1u) ? -__builtin_inff() : 0.f);
+      scored();
       return;
     }
     f16x8 av[NKS];
@@ -213,73 +230,173 @@ __global__ __launch_bounds__(NW * 64) void pq_mfma_kernel(PqParams P) {
           __builtin_amdgcn_ubfe(PqCodes<M>::word(cv, (c * 32 / DSUB) >> 2), lsh[c], 8);
       av[c] = __builtin_bit_cast(f16x8, *(const u32x4*)(cbl + lbase[c] + code * (DSUB * 2)));
     }
-    // k-step outer, query block inner: NQB independent accumulation chains
-    // keep the matrix pipe busy between dependent MFMAs
-    f32x4 acc[NQB];
+    // CH query blocks at a time, k-step outer: independent accumulation
+    // chains keep the matrix pipe busy between dependent MFMAs, and no more
+    // accumulators than that are live
+    constexpr int CH = NB % 2 == 0 ? 2 : NB;
 #pragma unroll
-    for (int nb = 0; nb < NQB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b0 = 0; b0 < NB; b0 += CH) {
+      f32x4 acc[CH];
 #pragma unroll
-    for (int c = 0; c < NKS; ++c)
+      for (int nb = 0; nb < CH; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int nb = 0; nb < NQB; ++nb)
-        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[c], qb[nb][c], acc[nb], 0, 0, 0);
+      for (int c = 0; c < NKS; ++c)
 #pragma unroll
-    for (int nb = 0; nb < NQB; ++nb)
-      mx[nb] = fmaxf(mx[nb], fmaxf(fmaxf(acc[nb].x, acc[nb].y), fmaxf(acc[nb].z, acc[nb].w)));
+        for (int nb = 0; nb < CH; ++nb)
+          acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[c], qb[b0 + nb][c], acc[nb], 0, 0, 0);
+#pragma unroll
+      for (int nb = 0; nb < CH; ++nb)
+        mx[b0 + nb] = fmaxf(fmaxf(fmaxf(fmaxf(mx[b0 + nb], acc[nb].x), acc[nb].y), acc[nb].z),
+                            acc[nb].w);
+    }
     if (fl & F_DLAST) {
       float qsum = 0.f;
 #pragma unroll
-      for (int nb = 0; nb < NQB; ++nb) {
+      for (int nb = 0; nb < NB; ++nb) {
         const float v = max_rows4(mx[nb]);
         qsum += v;
         mx[nb] = -__builtin_inff();
         if ((nb + 1) % bpq == 0) {
-          const int gq = nb / bpq;
-          float t = qsum;
-          t = row_sum16(t);
-          if (lane == 0 && ((valid_m >> gq) & 1u)) store(pp, gq, t);
+          put(nb, row_sum16(qsum));
           qsum = 0.f;
         }
       }
+      scored();
     }
   };
 
-  // four ring slots, written out so each keeps its own registers
-  cvec r0, r1, r2, r3;
-  int f0, f1, f2, f3;
-  int64_t q0p, q1p, q2p, q3p;
-  fill(r0, f0, q0p);
-  fill(r1, f1, q1p);
-  fill(r2, f2, q2p);
-  fill(r3, f3, q3p);
-  if (f0 & F_VALID) {
-    while (true) {
-      consume(r0, f0, q0p);
-      fill(r0, f0, q0p);
-      consume(r1, f1, q1p);
-      fill(r1, f1, q1p);
-      consume(r2, f2, q2p);
-      fill(r2, f2, q2p);
-      consume(r3, f3, q3p);
-      fill(r3, f3, q3p);
-      if (!(f0 & F_VALID)) break;
+  vmem_wait<0>();  // the query operand is in its registers
+  int fl[PF];
+#pragma unroll
+  for (int k = 0; k < PF; ++k) fl[k] = refill(k);
+  vmem_wait<PF - 1>();
+  cvec cv = *(const cvec*)(ring + r * M);
+  // a step: the next tile's codes out of its slot, this tile's slot refilled
+  // (its codes are in registers), then the arithmetic
+  while (fl[0] & F_VALID) {
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {
+      vmem_wait<PF - 2>();
+      const cvec nx = *(const cvec*)(ring + ((k + 1) % PF) * SLOT + r * M);
+      const int f = fl[k];
+      fl[k] = refill(k);
+      consume(cv, f);
+      cv = nx;
     }
+  }
+  // the idle refills still target this wave's ring
+  vmem_wait<0>();
+  flush(n_out & 63);
+}
+
+// First position of wave w of W: equal shares of the document tokens of every
+// query group (positions are group * n_docs + document), or of the candidates
+// of all queries.
+__device__ int64_t pq_range_begin(const PqParams& P, int64_t w, int64_t W, int64_t n) {
+  if (w >= W) return n;
+  if (P.cand_off != nullptr || P.tokens_per_query <= 0) return (n / W) * w + ((n % W) * w) / W;
+  const int64_t T = P.tokens_per_query, total = (n / P.n_docs) * T;
+  const int64_t tau = (total / W) * w + ((total % W) * w) / W;
+  const int64_t u = tau / T;
+  return u * P.n_docs + wave_lower_bound(P.d_off, P.n_docs, tau - u * T);
+}
+
+template <int M, int DSUB, int NQB, int NW>
+__global__ __launch_bounds__(NW * 64, NQB * M * DSUB <= 512 ? 4 : 2) void pq_mfma_kernel(PqParams P) {
+  extern __shared__ u32x4 cb_lds[];  // codebooks [M][K][DSUB] FP16
+  // ---- codebooks into LDS (16-byte copies) ----
+  {
+    const int n16 = M * P.K * DSUB * 2 / 16;
+    const u32x4* src = (const u32x4*)P.codebooks;
+    for (int e = threadIdx.x; e < n16; e += NW * 64) cb_lds[e] = src[e];
+  }
+  const int gsz = P.group;  // queries per group
+  const int64_t n = P.cand_off != nullptr ? P.n_pairs : ((P.n_q + gsz - 1) / gsz) * P.n_docs;
+  const int64_t w = (int64_t)blockIdx.x * NW + uniform(threadIdx.x >> 6);
+  const int64_t W = (int64_t)gridDim.x * NW;
+  int64_t pb = uniform64(pq_range_begin(P, w, W, n));
+  const int64_t pe = uniform64(pq_range_begin(P, w + 1, W, n));
+  __syncthreads();
+  const char* cbl = (const char*)cb_lds;
+  char* ring = (char*)cb_lds + M * P.K * DSUB * 2 +
+               uniform(threadIdx.x >> 6) * pq_mfma_wave_lds(M, NQB);
+  float* sc = (float*)(ring + PF * 16 * M);
+  const char* const zrow = zero_row_ptr();
+  // the group-sized pieces of this wave's range
+  while (pb < pe) {
+    int64_t a0, base, end;  // first query, the position documents count from
+    if (P.cand_off == nullptr) {
+      const int64_t u = pb / P.n_docs;
+      a0 = u * gsz;
+      base = u * P.n_docs;
+      end = base + P.n_docs;
+    } else {
+      // (positions that no query owns, which only offsets breaking the
+      // contract leave, are passed over)
+      a0 = uniform64(wave_owner(P.cand_off, P.n_q, pb));
+      base = 0;
+      end = uniform64(P.cand_off[a0 + 1]);
+      if (a0 < 0) {
+        pb = end;
+        continue;
+      }
+      if (end <= pb) break;
+    }
+    const int64_t hi = end < pe ? end : pe;
+    // a query alone in its group runs with its own block count, not its
+    // batch's longest query's
+    int own = NQB;
+    if (gsz == 1) {
+      const int nq = uniform((int)(P.q_off[a0 + 1] - P.q_off[a0]));
+      own = nq <= 16 ? 1 : (nq + 15) / 16;
+    }
+    if (NQB > 1 && NQB <= 4 && own == 1)
+      score_range<M, DSUB, 1>(P, a0, gsz, 1, base, pb, hi, cbl, ring, sc, zrow);
+    else if (NQB > 2 && NQB <= 4 && own == 2)
+      score_range<M, DSUB, 2>(P, a0, gsz, 2, base, pb, hi, cbl, ring, sc, zrow);
+    else if (NQB > 3 && NQB <= 4 && own == 3)
+      score_range<M, DSUB, 3>(P, a0, gsz, 3, base, pb, hi, cbl, ring, sc, zrow);
+    else
+      score_range<M, DSUB, NQB>(P, a0, gsz, P.bpq, base, pb, hi, cbl, ring, sc, zrow);
+    pb = hi;
   }
 }
 
-template <int M, int DSUB, int NQB>
-hipError_t launch_mfma_t(const PqParams& P, size_t lds, hipStream_t s) {
-  constexpr int NW = 8;
+template <int M, int DSUB, int NQB, int NW>
+hipError_t launch_mfma_w(const PqParams& P, size_t lds, hipStream_t s) {
   auto k = pq_mfma_kernel<M, DSUB, NQB, NW>;
   if (lds > 64 * 1024) {
     hipError_t e =
         hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  const int64_t n_groups = (P.n_q + P.group - 1) / P.group;
-  const int64_t items = n_groups * P.n_chunks;
-  hipLaunchKernelGGL(k, dim3((unsigned)items), dim3(NW * 64), lds, s, P);
+  int occ = 0;
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k, NW * 64, lds);
+  if (e != hipSuccess) return e;
+  // Every compute unit filled, down to about two documents per wave, and up
+  // to eight times as many workgroups where a wave keeps 200 documents to
+  // spread the copy of the codebooks over: 64 queries over 250K documents
+  // 7.95 / 7.36 / 7.24 ms with one, four and eight workgroups per place; 400K
+  // candidates of eight queries 422 / 424 / 443 us.
+  const int64_t n =
+      P.cand_off != nullptr ? P.n_pairs : (P.n_q + P.group - 1) / P.group * P.n_docs;
+  const int64_t resident = (int64_t)(occ < 1 ? 1 : occ) * P.cus;
+  int64_t times = n / (200 * NW * resident);
+  times = times < 1 ? 1 : (times > 8 ? 8 : times);
+  int64_t grid = times * resident;
+  const int64_t most = (n + 2 * NW - 1) / (2 * NW);
+  if (grid > most) grid = most;
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(NW * 64), lds, s, P);
   return hipGetLastError();
+}
+
+template <int M, int DSUB, int NQB>
+hipError_t launch_mfma_t(const PqParams& P, size_t lds, hipStream_t s) {
+  // two waves: only codebooks near the size of the LDS (M * dsub = 512)
+  if constexpr (M * DSUB >= 512) {
+    if (P.nw == 2) return launch_mfma_w<M, DSUB, NQB, 2>(P, lds, s);
+  }
+  return launch_mfma_w<M, DSUB, NQB, 8>(P, lds, s);
 }
 
 template <int M, int DSUB>
