@@ -161,7 +161,9 @@ __device__ void topk_epilogue(const FusedParams& P, u32x4* lds, const int64_t* r
   const int k = P.topk_k, cap = P.sel_cap, G = P.group;
   uint64_t* buf = (uint64_t*)lds;
   uint32_t* hist = (uint32_t*)((char*)lds + (size_t)cap * 8);
-  const uint32_t* lkeys = (const uint32_t*)((const char*)lds + P.lds_keys_off);
+  // (typed as LDS, so a read of it is never merged with one of the spill array)
+  const auto* lkeys = (const __attribute__((address_space(3))) uint32_t*)((const char*)lds +
+                                                                          P.lds_keys_off);
   const int key_slots = P.key_cap / NW;
   const int64_t lo = ranges[0], hi = ranges[2 * NW - 1];
   if (threadIdx.x == 0) P.wg_lo[blockIdx.x] = lo;
@@ -184,21 +186,23 @@ __device__ void topk_epilogue(const FusedParams& P, u32x4* lds, const int64_t* r
     if (p0 >= p1) continue;
     for (int gq = 0; gq < G; ++gq) {
       if (a * G + gq >= P.n_q) break;
-      auto get = [&](int64_t i) -> uint64_t {
+      auto lo32 = [&](int64_t i) -> uint32_t {
         const int64_t p = p0 + i;
-        const uint32_t id = dense ? (uint32_t)(p - s0) : (uint32_t)P.cand_ids[p];
-        if (contig) return rank_key(lkeys[(p - lo) * G + gq], id);
+        return ~(dense ? (uint32_t)(p - s0) : (uint32_t)P.cand_ids[p]);
+      };
+      auto hi32 = [&](int64_t i) -> uint32_t {
+        const int64_t p = p0 + i;
+        if (contig) return lkeys[(p - lo) * G + gq];
         int w = 0;  // the wave whose range holds p: the last one starting at or before it
 #pragma unroll
         for (int v = 1; v < NW; ++v)
           if (ranges[v] <= p) w = v;
         const int64_t wl = ranges[w], wh = ranges[NW + w];
-        const uint32_t key = (wh - wl) * G <= key_slots ? lkeys[w * key_slots + (p - wl) * G + gq]
-                                                        : P.key_spill[p * G + gq];
-        return rank_key(key, id);
+        return (wh - wl) * G <= key_slots ? lkeys[w * key_slots + (p - wl) * G + gq]
+                                          : P.key_spill[p * G + gq];
       };
       const int64_t slot = ((int64_t)blockIdx.x + a) * G + gq;
-      const int cnt = block_topk(p1 - p0, k, get, hist, buf, cap, P.part_keys + slot * k);
+      const int cnt = block_topk<1>(p1 - p0, k, hi32, lo32, hist, buf, cap, P.part_keys + slot * k);
       if (threadIdx.x == 0) P.part_cnt[slot] = (uint32_t)cnt;
     }
   }

@@ -3,7 +3,14 @@
 // Every entry maps to a 64-bit key that orders exactly like the required
 // ranking: the high 32 bits are the score's bits made order-preserving as an
 // unsigned integer (NaN -> 0, below -inf), the low 32 bits are ~id so smaller
-// ids rank higher. Five launches:
+// ids rank higher. Two forms, chosen in launch_topk:
+//
+// Two launches, for segments that a few workgroups can read: each workgroup
+// selects the k best keys of one share of a segment (part), and one workgroup
+// per segment merges the segment's parts (as the fused scorer's top-k does
+// with the parts of its workgroups).
+//
+// Five launches, for longer segments:
 //   init     zero the per-segment histograms and counters;
 //   hist0    4096-bin histogram of the top 12 key bits (LDS, then global);
 //   hist1    each block re-derives the bin b0 holding the k-th largest entry
@@ -18,13 +25,14 @@
 //            workgroup instead finishes the selection with 8-bit radix passes
 //            over the segment, which is slower but exact.
 // Integer keys only: the result is exact and independent of launch shape.
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 #include "select_impl.h"
 
 namespace {
 
-using topk_detail::bitonic_desc;
 using topk_detail::key_score;
 using topk_detail::score_key;
 
@@ -206,20 +214,20 @@ __global__ __launch_bounds__(TK_SORT_THREADS) void topk_sort_kernel(
   int count;  // keys placed at the front of `keys`, already the top `count`
   if (n <= k) {
     count = (int)n;
-    int p2 = 1;
+    int p2 = 64;
     while (p2 < count) p2 <<= 1;
     for (int i = threadIdx.x; i < p2; i += blockDim.x) keys[i] = i < count ? above[i] : 0ull;
     __syncthreads();
-    bitonic_desc(keys, p2);
+    topk_detail::bitonic_desc<4>(keys, p2);
   } else if (w->n_bound <= BOUND_CAP) {
     const int na = (int)w->n_above, nb = (int)w->n_bound;
     const int tot = na + nb;
-    int p2 = 1;
+    int p2 = 64;
     while (p2 < tot) p2 <<= 1;
     for (int i = threadIdx.x; i < p2; i += blockDim.x)
       keys[i] = i < na ? above[i] : (i < tot ? bound[i - na] : 0ull);
     __syncthreads();
-    bitonic_desc(keys, p2);
+    topk_detail::bitonic_desc<4>(keys, p2);
     count = k;
   } else {
     // Boundary overflow: the top-k all have key >= (P << 40); finish the
@@ -263,11 +271,11 @@ __global__ __launch_bounds__(TK_SORT_THREADS) void topk_sort_kernel(
     }
     __syncthreads();
     const int got = s_cnt[1] < (uint32_t)SORT_CAP ? (int)s_cnt[1] : SORT_CAP;
-    int p2 = 1;
+    int p2 = 64;
     while (p2 < got || p2 < k) p2 <<= 1;
     for (int i = got + threadIdx.x; i < p2; i += blockDim.x) keys[i] = 0ull;
     __syncthreads();
-    bitonic_desc(keys, p2);
+    topk_detail::bitonic_desc<4>(keys, p2);
     count = k;
   }
   for (int i = threadIdx.x; i < k; i += blockDim.x) {
@@ -285,50 +293,99 @@ __global__ __launch_bounds__(TK_SORT_THREADS) void topk_sort_kernel(
 
 }  // namespace
 
-size_t topk_ws_bytes(int64_t n_seg, int k) {
-  (void)k;
-  return (size_t)n_seg * seg_ws_bytes();
-}
-
-hipError_t launch_topk(const float* scores, const int64_t* seg_off, int64_t n_seg, int64_t n_total,
-                       const int32_t* ids, int k, float* out_scores, int32_t* out_ids, void* ws,
-                       hipStream_t st) {
-  if (n_seg == 0) return hipSuccess;
-  int64_t avg = n_total / n_seg;
-  int64_t bps = avg / (TK_THREADS * 16);
-  if (bps < 1) bps = 1;
-  if (bps > 256) bps = 256;
-  const dim3 grid((unsigned)bps, (unsigned)n_seg);
-  hipLaunchKernelGGL(topk_init_kernel, dim3((unsigned)n_seg), dim3(TK_THREADS), 0, st, ws);
-  hipLaunchKernelGGL(topk_hist0_kernel, grid, dim3(TK_THREADS), 0, st, scores, seg_off, ws, k);
-  hipLaunchKernelGGL(topk_hist1_kernel, grid, dim3(TK_THREADS), 0, st, scores, seg_off, ws, k);
-  hipLaunchKernelGGL(topk_compact_kernel, grid, dim3(TK_THREADS), 0, st, scores, seg_off, ids, ws,
-                     k);
-  hipLaunchKernelGGL(topk_sort_kernel, dim3((unsigned)n_seg), dim3(TK_SORT_THREADS), 0, st, scores,
-                     seg_off, ids, ws, k, out_scores, out_ids);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
-// Merge of the fused scorer's top-k parts: one workgroup per query. The
-// workgroups of the scoring launch whose ranges cover the query's work pairs
-// [ps, pe) are b0 .. b1 (wg_lo is non-decreasing); each non-empty one left
-// the k best keys of its share in part slot (b + unit) * group + query of the
-// unit. Missing part entries read as key 0, below every real key, so the
-// query's top-k is the top-k of the concatenated parts; key 0 in the result
-// means fewer than k candidates and becomes (-inf, -1).
+// Merging sorted parts: parts 0 .. nb-1 hold cnt(b) <= k keys each at part(b),
+// descending; the k best of all of them, sorted, become a result row. Key 0,
+// below every real key, means fewer than k entries and becomes (-inf, -1).
 // ---------------------------------------------------------------------------
 namespace {
 
 constexpr int MERGE_THREADS = 1024;
-constexpr int MERGE_CAP = 2048;  // sort buffer: >= 2 * max k
+constexpr int MERGE_GATHER = 4032;  // keys gathered from the parts
+constexpr int MERGE_CAP = 1024;     // sort buffer: one key per thread, >= max k
 static_assert(MERGE_MAX_GRID % MERGE_THREADS == 0, "extras per thread");
 
+// the sort buffer of a selection of k keys: the smallest that holds them (a
+// selection sorts little more than k keys)
+__device__ __forceinline__ int sort_cap(int k) {
+  int c = 64;
+  while (c < k) c <<= 1;
+  return c;
+}
+
+// gat: MERGE_GATHER keys, buf: MERGE_CAP keys, hist: SEL_HIST_WORDS words.
+template <class Cnt, class Part>
+__device__ __forceinline__ void merge_parts(int nb, int k, Cnt cnt, Part part, uint32_t* hist,
+                                            uint64_t* gat, uint64_t* buf, float* os, int32_t* oi) {
+  using namespace topk_detail;
+  // Fast path: the k best of the first m keys of every part (each part is
+  // sorted) are the answer when no part holds a key left out that could reach
+  // it, i.e. when every part with more than m keys has its (m+1)-th key below
+  // the k-th of the result. Each part holds about k / nb of the answer on
+  // average, so m of twice that plus six rarely misses (and a miss takes the
+  // exact path below).
+  int m = 2 * ((k + nb - 1) / nb) + 6;
+  m = m < MERGE_GATHER / nb ? m : MERGE_GATHER / nb;
+  m = m < k ? m : k;
+  bool done = false;
+  int got = 0;
+  if (m >= 1) {
+    const int n = nb * m;
+    for (int i = threadIdx.x; i < n; i += MERGE_THREADS) {
+      const int bi = i / m, j = i - bi * m;
+      gat[i] = (uint32_t)j < cnt(bi) ? part(bi)[j] : 0ull;
+    }
+    // the (m+1)-th key of the parts that have one, loaded in the same round
+    // (nb <= MERGE_MAX_GRID = 4 x MERGE_THREADS)
+    uint64_t ex[MERGE_MAX_GRID / MERGE_THREADS];
+#pragma unroll
+    for (int q = 0; q < MERGE_MAX_GRID / MERGE_THREADS; ++q) {
+      const int bi = threadIdx.x + q * MERGE_THREADS;
+      ex[q] = (bi < nb && cnt(bi) > (uint32_t)m) ? part(bi)[m] : 0ull;
+    }
+    __syncthreads();
+    got = block_topk<1>(n, k, [&](int64_t i) { return (uint32_t)(gat[i] >> 32); },
+                        [&](int64_t i) { return (uint32_t)gat[i]; }, hist, buf, sort_cap(k), buf);
+    const uint64_t kth = k <= got ? buf[k - 1] : 0ull;  // 0: fewer than k keys gathered
+    int ok = 1;
+#pragma unroll
+    for (int q = 0; q < MERGE_MAX_GRID / MERGE_THREADS; ++q) {
+      const int bi = threadIdx.x + q * MERGE_THREADS;
+      if (bi < nb && cnt(bi) > (uint32_t)m && ex[q] >= kth) ok = 0;
+    }
+    done = __syncthreads_and(ok) != 0;
+  }
+  if (!done) {
+    auto slot = [&](int64_t i) -> uint64_t {
+      const int bi = (int)(i / k);
+      const int j = (int)(i - (int64_t)bi * k);
+      return (uint32_t)j < cnt(bi) ? part(bi)[j] : 0ull;
+    };
+    got = block_topk<1>((int64_t)nb * k, k, [&](int64_t i) { return (uint32_t)(slot(i) >> 32); },
+                        [&](int64_t i) { return (uint32_t)slot(i); }, hist, buf, sort_cap(k), buf);
+  }
+  for (int i = threadIdx.x; i < k; i += MERGE_THREADS) {
+    const uint64_t key = i < got ? buf[i] : 0ull;
+    os[i] = key == 0ull ? -__builtin_inff() : key_score((uint32_t)(key >> 32));
+    oi[i] = key == 0ull ? -1 : key_id(key);
+  }
+}
+
+// Merge of the fused scorer's top-k parts: one workgroup per query. The
+// workgroups of the scoring launch whose ranges cover the query's work pairs
+// [ps, pe) are b0 .. b1 (wg_lo is non-decreasing); each non-empty one left
+// the k best keys of its share in part slot (b + unit) * group + query of the
+// unit.
+// Bound: latency (two rounds of loads from other XCDs' writes and a sort).
+// One query, k = 100, 250 parts: 14.3 us, 20.4 with the sort in 55 barrier'd
+// passes over LDS; k = 1000: 19 us, 290 to 390 with the radix
+// select that more than 4,000 gathered keys fell back to.
 __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M) {
   using namespace topk_detail;
+  __shared__ uint64_t gat[MERGE_GATHER];
   __shared__ uint64_t buf[MERGE_CAP];
   __shared__ uint32_t hist[SEL_HIST_WORDS];
-  __shared__ uint32_t cnts[MERGE_MAX_GRID];
+  __shared__ uint16_t cnts[MERGE_MAX_GRID];  // at most k <= 1024
   const int64_t qa = blockIdx.x;
   const int G = M.group, k = M.k;
   const bool dense = M.cand_off == nullptr;
@@ -359,7 +416,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
     const uint32_t c = M.part_cnt[(b + a) * G + gq];
     c0 += r <= ps ? 1u : 0u;
     c1 += r <= pe - 1 ? 1u : 0u;
-    cnts[b] = r < r1 ? c : 0u;
+    cnts[b] = (uint16_t)(r < r1 ? c : 0u);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -378,55 +435,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
     return M.part_keys + ((b0 + bi + a) * G + gq) * (int64_t)k;
   };
   auto cnt = [&](int bi) -> uint32_t { return cnts[b0 + bi]; };
-  // Fast path: the first m keys of every part (each part is sorted), sorted
-  // together; their top k is the answer when no part holds a key left out
-  // that could reach it, i.e. when every part with more than m keys has its
-  // (m+1)-th key below the k-th of the result. Each part holds about k / nb
-  // of the answer on average, so m of twice that plus two rarely misses (and
-  // a miss takes the exact path below).
-  int m = 2 * ((k + nb - 1) / nb) + 2;
-  m = m < k ? m : k;
-  m = m < MERGE_CAP / nb ? m : MERGE_CAP / nb;
-  bool done = false;
-  if (m >= 1 && m < k) {
-    int p2 = 64;
-    while (p2 < nb * m) p2 <<= 1;
-    for (int i = threadIdx.x; i < p2; i += MERGE_THREADS) {
-      const int bi = i / m, j = i - bi * m;
-      buf[i] = (i < nb * m && (uint32_t)j < cnt(bi)) ? part(bi)[j] : 0ull;
-    }
-    // the (m+1)-th key of the parts that have one, loaded in the same round
-    // (nb <= MERGE_MAX_GRID = 4 x MERGE_THREADS)
-    uint64_t ex[MERGE_MAX_GRID / MERGE_THREADS];
-#pragma unroll
-    for (int q = 0; q < MERGE_MAX_GRID / MERGE_THREADS; ++q) {
-      const int bi = threadIdx.x + q * MERGE_THREADS;
-      ex[q] = (bi < nb && cnt(bi) > (uint32_t)m) ? part(bi)[m] : 0ull;
-    }
-    __syncthreads();
-    bitonic_desc(buf, p2);
-    const uint64_t kth = buf[k - 1];  // 0: fewer than k keys gathered
-    int ok = 1;
-#pragma unroll
-    for (int q = 0; q < MERGE_MAX_GRID / MERGE_THREADS; ++q) {
-      const int bi = threadIdx.x + q * MERGE_THREADS;
-      if (bi < nb && cnt(bi) > (uint32_t)m && ex[q] >= kth) ok = 0;
-    }
-    done = __syncthreads_and(ok) != 0;
-  }
-  if (!done) {
-    auto get = [&](int64_t i) -> uint64_t {
-      const int bi = (int)(i / k);
-      const int j = (int)(i - (int64_t)bi * k);
-      return (uint32_t)j < cnt(bi) ? part(bi)[j] : 0ull;
-    };
-    block_topk((int64_t)nb * k, k, get, hist, buf, MERGE_CAP, buf);
-  }
-  for (int i = threadIdx.x; i < k; i += MERGE_THREADS) {
-    const uint64_t key = buf[i];
-    os[i] = key == 0ull ? -__builtin_inff() : key_score((uint32_t)(key >> 32));
-    oi[i] = key == 0ull ? -1 : key_id(key);
-  }
+  merge_parts(nb, k, cnt, part, hist, gat, buf, os, oi);
 }
 
 }  // namespace
@@ -438,5 +447,110 @@ size_t fused_topk_scratch_bytes(int sel_cap) {
 hipError_t launch_topk_merge(const MergeParams& M, hipStream_t st) {
   if (M.n_q <= 0) return hipSuccess;
   hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)M.n_q), dim3(MERGE_THREADS), 0, st, M);
+  return hipGetLastError();
+}
+// ---------------------------------------------------------------------------
+// Top-k of segments that a few workgroups' shares cover: each workgroup leaves
+// the k best keys of its share of a segment, sorted, and one workgroup per
+// segment merges them: two launches.
+// ---------------------------------------------------------------------------
+namespace {
+
+constexpr int PART_SCORES = 6144;  // score keys of a share kept in LDS
+
+// Parts of a segment in its workspace: np counts, then np times k keys.
+__device__ __forceinline__ uint32_t* part_counts(void* ws, int64_t s) { return (uint32_t*)seg_ws(ws, s); }
+__device__ __forceinline__ uint64_t* part_keys(void* ws, int64_t s, int np) {
+  return (uint64_t*)((char*)seg_ws(ws, s) + (((size_t)np * 4 + 15) & ~(size_t)15));
+}
+int max_parts(int k) { return (int)((seg_ws_bytes() - 16) / ((size_t)k * 8 + 4)); }
+
+__global__ __launch_bounds__(MERGE_THREADS) void topk_part_kernel(
+    const float* __restrict__ scores, const int64_t* __restrict__ seg_off,
+    const int32_t* __restrict__ ids, void* ws, int k, int np) {
+  using namespace topk_detail;
+  __shared__ uint64_t buf[MERGE_CAP];
+  __shared__ uint32_t hist[SEL_HIST_WORDS];
+  __shared__ uint32_t sk[PART_SCORES];
+  const int64_t s = blockIdx.y;
+  const int b = blockIdx.x;
+  const int64_t start = seg_off[s], len = seg_off[s + 1] - start;
+  const int64_t share = (len + np - 1) / np;
+  const int64_t lo = share * b < len ? share * b : len;
+  const int64_t n = (len - lo < share ? len - lo : share);
+  const float* sc = scores + start + lo;
+  int count = 0;
+  if (n > 0) {
+    auto low = [&](int64_t i) -> uint32_t {
+      return ~(ids ? (uint32_t)ids[start + lo + i] : (uint32_t)(lo + i));
+    };
+    uint64_t* out = part_keys(ws, s, np) + (int64_t)b * k;
+    if (n <= PART_SCORES) {
+      for (int i = threadIdx.x; i < n; i += MERGE_THREADS) sk[i] = score_key(sc[i]);
+      __syncthreads();
+      count = block_topk<1>(n, k, [&](int64_t i) { return sk[i]; }, low, hist, buf, sort_cap(k), out);
+    } else {
+      count = block_topk<1>(n, k, [&](int64_t i) { return score_key(sc[i]); }, low, hist, buf,
+                            sort_cap(k), out);
+    }
+  }
+  if (threadIdx.x == 0) part_counts(ws, s)[b] = (uint32_t)count;
+}
+
+__global__ __launch_bounds__(MERGE_THREADS) void topk_part_merge_kernel(
+    void* ws, int k, int np, float* __restrict__ out_scores, int32_t* __restrict__ out_ids) {
+  using namespace topk_detail;
+  __shared__ uint64_t gat[MERGE_GATHER];
+  __shared__ uint64_t buf[MERGE_CAP];
+  __shared__ uint32_t hist[SEL_HIST_WORDS];
+  __shared__ uint16_t cnts[MERGE_MAX_GRID];
+  const int64_t s = blockIdx.x;
+  const uint32_t* counts = part_counts(ws, s);
+  for (int b = threadIdx.x; b < np; b += MERGE_THREADS) cnts[b] = (uint16_t)counts[b];
+  __syncthreads();
+  const uint64_t* keys = part_keys(ws, s, np);
+  merge_parts(
+      np, k, [&](int b) -> uint32_t { return cnts[b]; },
+      [&](int b) -> const uint64_t* { return keys + (int64_t)b * k; }, hist, gat, buf,
+      out_scores + s * k, out_ids + s * k);
+}
+
+}  // namespace
+
+size_t topk_ws_bytes(int64_t n_seg, int k) {
+  (void)k;
+  return (size_t)n_seg * seg_ws_bytes();
+}
+
+hipError_t launch_topk(const float* scores, const int64_t* seg_off, int64_t n_seg, int64_t n_total,
+                       const int32_t* ids, int k, float* out_scores, int32_t* out_ids, void* ws,
+                       hipStream_t st) {
+  if (n_seg == 0) return hipSuccess;
+  const int64_t avg = n_total / n_seg;
+  // Shares of about PART_SCORES scores, as many as the workspace has room for
+  // the parts of; where that makes a share longer than four times that
+  // (k = 1000 from about 220K scores a segment on), the histogram launches.
+  // Eight segments of 1K to 94K scores, k = 100: 32 us against 65.
+  const int64_t np =
+      std::min<int64_t>(std::max<int64_t>(1, (avg + PART_SCORES - 1) / PART_SCORES),
+                        std::min(max_parts(k), MERGE_MAX_GRID));
+  if (avg <= np * PART_SCORES * 4) {
+    hipLaunchKernelGGL(topk_part_kernel, dim3((unsigned)np, (unsigned)n_seg), dim3(MERGE_THREADS),
+                       0, st, scores, seg_off, ids, ws, k, (int)np);
+    hipLaunchKernelGGL(topk_part_merge_kernel, dim3((unsigned)n_seg), dim3(MERGE_THREADS), 0, st,
+                       ws, k, (int)np, out_scores, out_ids);
+    return hipGetLastError();
+  }
+  int64_t bps = avg / (TK_THREADS * 16);
+  if (bps < 1) bps = 1;
+  if (bps > 256) bps = 256;
+  const dim3 grid((unsigned)bps, (unsigned)n_seg);
+  hipLaunchKernelGGL(topk_init_kernel, dim3((unsigned)n_seg), dim3(TK_THREADS), 0, st, ws);
+  hipLaunchKernelGGL(topk_hist0_kernel, grid, dim3(TK_THREADS), 0, st, scores, seg_off, ws, k);
+  hipLaunchKernelGGL(topk_hist1_kernel, grid, dim3(TK_THREADS), 0, st, scores, seg_off, ws, k);
+  hipLaunchKernelGGL(topk_compact_kernel, grid, dim3(TK_THREADS), 0, st, scores, seg_off, ids, ws,
+                     k);
+  hipLaunchKernelGGL(topk_sort_kernel, dim3((unsigned)n_seg), dim3(TK_SORT_THREADS), 0, st, scores,
+                     seg_off, ids, ws, k, out_scores, out_ids);
   return hipGetLastError();
 }
