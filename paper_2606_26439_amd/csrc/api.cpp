@@ -91,10 +91,13 @@ DevInfo device_info() {
 
 // ---------------------------------------------------------------- tuning --
 
+// units: 0 when a launch has one query unit, 1 when several units re-read the
+// same documents (those come from the caches then, not from HBM). A cache
+// entry without it holds for both until one with it says otherwise.
 struct TuneKey {
-  int dt, dim, nqb;
+  int dt, dim, nqb, units;
   bool operator<(const TuneKey& o) const {
-    return std::tie(dt, dim, nqb) < std::tie(o.dt, o.dim, o.nqb);
+    return std::tie(dt, dim, nqb, units) < std::tie(o.dt, o.dim, o.nqb, o.units);
   }
 };
 struct FusedCfg {
@@ -134,36 +137,6 @@ struct ResCfg {
   int pipe = -1;  // variant (-1: automatic)
 };
 std::map<ResKey, ResCfg> g_res_tuned;
-
-// Untuned keys: document tiles staged through LDS (the faster form measured on
-// MI355X for every element type but FP32) when the ring fits beside the query
-// block, else register-direct.
-FusedCfg default_cfg(int dt, size_t q_lds, int dch) {
-  FusedCfg c;
-  c.nw = 4;
-  c.wg_per_cu = 0;
-  if (dt == MAXSIM_F32) {
-    c.pf = 2;
-    c.stage = 0;
-    return c;
-  }
-  c.pf = 3;
-  c.stage = 1;
-  if (q_lds + (size_t)c.nw * c.pf * 16 * dch * esize(dt) > device_info().max_lds) {
-    c.pf = 4;
-    c.stage = 0;
-  }
-  return c;
-}
-
-FusedCfg lookup_cfg(const TuneKey& k, size_t q_lds, int dch) {
-  {
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tuned.find(k);
-    if (it != g_tuned.end()) return it->second;
-  }
-  return default_cfg(k.dt, q_lds, dch);
-}
 
 // ------------------------------------------------------------ fused plan --
 
@@ -258,6 +231,73 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
   return MAXSIM_OK;
 }
 
+// Untuned keys, by what was measured on MI355X (32-token queries over ragged
+// documents unless said):
+//   * the register-direct form with three steps in flight and eight waves
+//     where documents do not come from HBM at one read each: several units of
+//     eight query blocks (16 queries, 100K documents: 0.94 against 1.03 ms
+//     staged; one unit: 2.92 against 2.87, staged), chunk rows of at most 128
+//     bytes against four or more blocks (FP8 d = 128, four queries: 109
+//     against 130 us), 64-wide chunks of a d that is no multiple of 128
+//     (FP16 d = 400: 629 against 872 us);
+//   * FP32: staged, eight waves (two-query units 1.92 against 2.13 ms) where
+//     the ring fits, else register-direct;
+//   * else staged when the ring fits beside the query block.
+FusedCfg default_cfg(const FusedPlan& pl, int units) {
+  const int esz = esize(pl.dt);
+  const size_t q_lds = pl.qreg ? 0 : pl.lds, max_lds = device_info().max_lds;
+  auto ring = [&](int nw, int pf) { return q_lds + (size_t)nw * pf * 16 * pl.dch * esz; };
+  FusedCfg c;
+  c.nw = 4;
+  c.wg_per_cu = 0;
+  if (pl.dt == MAXSIM_F32) {
+    c.pf = 2;
+    c.stage = 0;
+    if (pl.qreg && ring(8, 2) <= max_lds) {
+      c.nw = 8;
+      c.wg_per_cu = 1;
+      c.stage = 1;
+    }
+    return c;
+  }
+  if ((pl.dch == 64 && pl.P.nch > 1) || (pl.qreg && pl.nqb >= 4 && pl.dch * esz <= 128) ||
+      (pl.nqb == 8 && units)) {
+    c.pf = 3;
+    c.nw = 8;
+    c.wg_per_cu = pl.nqb == 8 ? 2 : 1;
+    c.stage = 0;
+    return c;
+  }
+  if (pl.nqb == 8) {
+    c.pf = 2;
+    c.nw = 8;
+    c.wg_per_cu = 2;
+    c.stage = 1;
+    return c;
+  }
+  c.pf = 3;
+  c.stage = 1;
+  if (ring(c.nw, c.pf) > max_lds) {
+    c.pf = 4;
+    c.stage = 0;
+  }
+  return c;
+}
+
+TuneKey tune_key(const FusedPlan& pl) {
+  return {pl.dt, pl.P.dim, pl.nqb, !pl.P.cand_off && pl.P.n_units > 1 ? 1 : 0};
+}
+
+FusedCfg lookup_cfg(const FusedPlan& pl) {
+  const TuneKey k = tune_key(pl);
+  {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    auto it = g_tuned.find(k);
+    if (it != g_tuned.end()) return it->second;
+  }
+  return default_cfg(pl, k.units);
+}
+
 // A fused launch ready to go: kernel, parameters, dynamic LDS and grid.
 struct FusedLaunch {
   FusedFns fns{};
@@ -318,7 +358,7 @@ maxsim_status prepare_fused(const FusedPlan& pl, const FusedCfg& cfg, int topk_k
     P.topk_k = topk_k;
     P.sel_cap = std::min(2048, std::max(256, pow2_at_least(2 * topk_k)));
     const size_t head = (std::max(lds, fused_topk_scratch_bytes(P.sel_cap)) + 15) & ~(size_t)15;
-    const size_t ranges = (size_t)cfg.nw * 16;
+    const size_t ranges = (size_t)cfg.nw * 32;
     const size_t share = di.max_lds / (size_t)per_cu;
     int64_t slots = share > head + ranges ? (int64_t)((share - head - ranges) / 4) : 0;
     slots = std::min<int64_t>(slots, 65536);
@@ -336,6 +376,23 @@ maxsim_status prepare_fused(const FusedPlan& pl, const FusedCfg& cfg, int topk_k
   if (grid > need) grid = need;
   if (grid < 1) grid = 1;
   if (topk_k > 0 && grid > MERGE_MAX_GRID) grid = MERGE_MAX_GRID;
+  if (grid * cfg.nw > 0xffff) grid = 0xffff / cfg.nw;  // the kernel's shares are 32-bit products
+  // several units: their workgroups interleaved over the XCDs, where rounding
+  // the grid to whole rounds costs at most an eighth of it
+  P.spread = 1;
+  if (!P.cand_off && P.n_units > 1 && P.tokens_per_query > 0) {
+    const int64_t round = 8 * P.n_units, whole = grid / round * round;
+    if (whole > 0 && whole * 8 >= grid * 7) {
+      grid = whole;
+      P.spread = (int32_t)P.n_units;
+    }
+  }
+  const int64_t total = (P.cand_off || P.tokens_per_query <= 0)
+                            ? P.n_upairs
+                            : P.n_units * P.tokens_per_query;
+  const int64_t waves = grid * cfg.nw;
+  P.share_q = total / waves;
+  P.share_r = total % waves;
   L.fns = fns;
   L.P = P;
   L.lds = lds;
@@ -380,12 +437,13 @@ std::string cfg_json_all() {
   std::string out = "{\"version\":1,\"entries\":[";
   bool first = true;
   for (auto& kv : g_tuned) {
-    char b[192];
+    char b[224], units[24] = "";
+    if (kv.first.units) snprintf(units, sizeof units, ",\"units\":%d", kv.first.units);
     snprintf(b, sizeof b,
-             "%s{\"dtype\":%d,\"dim\":%d,\"nqb\":%d,\"pf\":%d,\"nw\":%d,\"wg_per_cu\":%d,"
+             "%s{\"dtype\":%d,\"dim\":%d,\"nqb\":%d%s,\"pf\":%d,\"nw\":%d,\"wg_per_cu\":%d,"
              "\"stage\":%d,\"rows\":%d}",
-             first ? "" : ",", kv.first.dt, kv.first.dim, kv.first.nqb, kv.second.pf, kv.second.nw,
-             kv.second.wg_per_cu, kv.second.stage, kv.second.rows);
+             first ? "" : ",", kv.first.dt, kv.first.dim, kv.first.nqb, units, kv.second.pf,
+             kv.second.nw, kv.second.wg_per_cu, kv.second.stage, kv.second.rows);
     out += b;
     first = false;
   }
@@ -463,7 +521,7 @@ maxsim_status maxsim_score(const maxsim_csr* queries, const maxsim_csr* docs,
   FusedPlan pl;
   maxsim_status st = plan_fused(queries, docs, cand, scores, pl);
   if (st) return st;
-  FusedCfg cfg = lookup_cfg({pl.dt, queries->dim, pl.nqb}, pl.qreg ? 0 : pl.lds, pl.dch);
+  FusedCfg cfg = lookup_cfg(pl);
   return run_fused(pl, cfg, (hipStream_t)stream);
 }
 
@@ -478,7 +536,7 @@ maxsim_status plan_score_topk(const maxsim_csr* q, const maxsim_csr* d,
   maxsim_status st = plan_fused(q, d, cand, nullptr, pl, true, /*need_scores=*/false);
   if (st) return st;
   if (pl.n_pairs > 0) {
-    FusedCfg cfg = lookup_cfg({pl.dt, q->dim, pl.nqb}, pl.qreg ? 0 : pl.lds, pl.dch);
+    FusedCfg cfg = lookup_cfg(pl);
     if ((st = prepare_fused(pl, cfg, k, L))) return st;
   } else {
     L.P = pl.P;
@@ -1340,8 +1398,15 @@ maxsim_status maxsim_load_tune_cache(const char* path) {
       if (!json_int(obj.c_str(), "stage", c.stage)) c.stage = 0;  // older caches
       if (!json_int(obj.c_str(), "rows", c.rows)) c.rows = 16;
       if ((c.pf >= 2 && c.pf <= 4) && (c.nw == 4 || c.nw == 8) && (c.stage == 0 || c.stage == 1) &&
-          (c.rows == 16 || c.rows == 32))
-        g_tuned[k] = c;
+          (c.rows == 16 || c.rows == 32)) {
+        const bool both = !json_int(obj.c_str(), "units", k.units);
+        if (both) k.units = 0;
+        if (k.units == 0 || k.units == 1) g_tuned[k] = c;
+        if (both) {
+          k.units = 1;
+          g_tuned[k] = c;
+        }
+      }
     }
     pos = end;
   }
@@ -1409,7 +1474,7 @@ maxsim_status maxsim_autotune(const maxsim_csr* queries, const maxsim_csr* docs,
                     std::to_string(queries->dim) + ",\"nqb\":" + std::to_string(pl.nqb) +
                     ",\"trials\":[";
   float best_ms = 1e30f;
-  FusedCfg best = default_cfg(pl.dt, pl.qreg ? 0 : pl.lds, pl.dch);
+  FusedCfg best = default_cfg(pl, tune_key(pl).units);
   bool first = true;
   for (const FusedCfg& c : space) {
     if (run_fused(pl, c, s)) continue;  // warm-up (also skips shapes that do not fit)
@@ -1443,7 +1508,7 @@ maxsim_status maxsim_autotune(const maxsim_csr* queries, const maxsim_csr* docs,
   std::string all;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tuned[{pl.dt, queries->dim, pl.nqb}] = best;
+    g_tuned[tune_key(pl)] = best;
     all = cfg_json_all();
   }
   if (cache_path) {

@@ -65,6 +65,18 @@ __device__ __forceinline__ float max_half_waves(float v) {
   return fmaxf(a, b);
 }
 __device__ __forceinline__ float max_rows4(float v) { return max_half_waves(max_row_pairs(v)); }
+// Two values at once: lanes 0-31 get max(a_i, a_i+32), lanes 32-63 the same of
+// b. The swap's two results are already different values, so no copies.
+__device__ __forceinline__ float max_halves_of2(float a, float b) {
+  asm volatile("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+  return fmaxf(a, b);
+}
+// Four values at once: row q (16 lanes) gets value q's max over the four rows.
+__device__ __forceinline__ float max_rows_of4(float v0, float v1, float v2, float v3) {
+  float a = max_halves_of2(v0, v2), b = max_halves_of2(v1, v3);
+  asm volatile("s_nop 3\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+  return fmaxf(a, b);
+}
 
 // Sum over the four 16-lane rows by the same two swaps, left in every lane:
 // (v_r0 + v_r1) + (v_r2 + v_r3), the pairs and order of an xor butterfly
@@ -125,6 +137,43 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int64_t* __restrict__ 
   uint64_t mask = __ballot(pred);
   int f = mask ? __ffsll((unsigned long long)mask) - 1 : (int)(hi - lo);
   return lo + f;
+}
+
+// wave_lower_bound of two keys at once: every round's loads of both searches
+// are in flight together.
+__device__ __forceinline__ void wave_lower_bound2(const int64_t* __restrict__ arr, int64_t n,
+                                                  int64_t key0, int64_t key1, int64_t& r0,
+                                                  int64_t& r1) {
+  const int lane = lane_id();
+  int64_t lo0 = 0, hi0 = n, lo1 = 0, hi1 = n;
+  // the bracket [lo, hi] of the first hit after a round of 64 probes
+  auto narrow = [&](int64_t& lo, int64_t& hi, int64_t step, uint64_t mask) {
+    if (mask & 1ull) {
+      hi = lo;
+    } else if (mask == 0) {
+      lo = lo + step * 63 + 1;
+    } else {
+      const int f = __ffsll((unsigned long long)mask) - 1;  // f >= 1
+      const int64_t pf = lo + step * f;
+      hi = pf < hi ? pf : hi;
+      lo = lo + step * (f - 1) + 1;
+    }
+  };
+  while (hi0 - lo0 >= 64 || hi1 - lo1 >= 64) {
+    const int64_t step0 = (hi0 - lo0 + 64) / 64, step1 = (hi1 - lo1 + 64) / 64;
+    int64_t p0 = lo0 + step0 * lane, p1 = lo1 + step1 * lane;
+    p0 = p0 < hi0 ? p0 : hi0;
+    p1 = p1 < hi1 ? p1 : hi1;
+    const int64_t v0 = arr[p0], v1 = arr[p1];
+    const uint64_t m0 = __ballot(v0 >= key0), m1 = __ballot(v1 >= key1);
+    narrow(lo0, hi0, step0, m0);
+    narrow(lo1, hi1, step1, m1);
+  }
+  const int64_t p0 = lo0 + lane, p1 = lo1 + lane;
+  const int64_t v0 = arr[p0 < hi0 ? p0 : hi0], v1 = arr[p1 < hi1 ? p1 : hi1];
+  const uint64_t m0 = __ballot(p0 <= hi0 && v0 >= key0), m1 = __ballot(p1 <= hi1 && v1 >= key1);
+  r0 = lo0 + (m0 ? __ffsll((unsigned long long)m0) - 1 : hi0 - lo0);
+  r1 = lo1 + (m1 ? __ffsll((unsigned long long)m1) - 1 : hi1 - lo1);
 }
 
 // Last index a in [0, n) with arr[a] <= key for arr non-decreasing of n + 1

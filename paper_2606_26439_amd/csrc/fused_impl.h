@@ -46,21 +46,33 @@ using ::DT_FP8;
 constexpr int F_VALID = 1, F_EMPTY = 2, F_TFIRST = 4, F_TLAST = 8, F_DLAST = 16, F_SPLIT = 32;
 constexpr int SPLIT_SHIFT = 24;  // rows of the ending document in a split tile
 
-// Work pair (unit, doc) where wave w of W starts: equal shares of the
-// document tokens (every unit reads all of them), or of the candidate pairs.
-__device__ int64_t wave_range_begin(const FusedParams& P, int64_t w, int64_t W) {
-  if (w >= W) return P.n_upairs;
-  if (P.cand_off != nullptr || P.tokens_per_query <= 0) {
-    return (P.n_upairs / W) * w + ((P.n_upairs % W) * w) / W;
+// Work pairs (unit, doc) [lo, hi) of wave w of W: equal shares of the document
+// tokens (every unit reads all of them), or of the candidate pairs. The host
+// divides the total by W (share_q, share_r; W < 2^16, so the remainder's part
+// is 32-bit arithmetic), and both ends are searched for at once: at the
+// smallest sizes the chain of loads before the first tile is most of a launch.
+__device__ __forceinline__ void wave_range(const FusedParams& P, uint32_t w, uint32_t W,
+                                           int64_t& lo, int64_t& hi) {
+  auto share = [&](uint32_t v) -> int64_t {
+    return P.share_q * v + (int64_t)(((uint32_t)P.share_r * v) / W);
+  };
+  int64_t t0 = share(w), t1 = share(w + 1);  // share(W) = the total
+  if (P.cand_off == nullptr && P.tokens_per_query > 0) {
+    const int64_t T = P.tokens_per_query;
+    int64_t a0 = 0, a1 = 0;
+    if (P.n_units > 1) {
+      a0 = t0 / T;
+      a1 = t1 / T;
+    }
+    const int64_t k0 = t0 - a0 * T, k1 = t1 - a1 * T;
+    int64_t b0, b1;
+    wave_lower_bound2(P.d_off, P.n_docs, k0, k1, b0, b1);
+    t0 = a0 * P.n_docs + b0;
+    t1 = a1 * P.n_docs + b1;
+    if (w + 1 == W) t1 = P.n_upairs;
   }
-  const int64_t T = P.tokens_per_query;
-  const int64_t total = P.n_units * T;
-  // tau = floor(w * total / W) without 128-bit arithmetic
-  int64_t tau = (total / W) * w + ((total % W) * w) / W;
-  int64_t a = tau / T;
-  int64_t rem = tau - a * T;
-  int64_t b = wave_lower_bound(P.d_off, P.n_docs, rem);
-  return a * P.n_docs + b;
+  lo = uniform64(t0);
+  hi = uniform64(t1);
 }
 
 template <int DT, int NL>
@@ -154,9 +166,11 @@ constexpr int lgkmcnt0_imm() { return 0xF | (0x3 << 14) | (0x7 << 4); }
 // of those pairs (exact radix select over the workgroup's contiguous key
 // array, or over the wave key slots and the spill array for waves whose
 // ranges did not fit them) go to the query's part slot.
-// ranges[w], ranges[NW + w]: first and end work pair of wave w (contiguous).
+// ranges[w], ranges[NW + w]: first and end work pair of wave w (contiguous);
+// with candidate lists ranges[2 NW + w], ranges[3 NW + w]: the queries of its
+// first and last pair. wg: the workgroup's place in the order of the pairs.
 template <int NW>
-__device__ void topk_epilogue(const FusedParams& P, u32x4* lds, const int64_t* ranges) {
+__device__ void topk_epilogue(const FusedParams& P, int64_t wg, u32x4* lds, const int64_t* ranges) {
   using namespace topk_detail;
   const int k = P.topk_k, cap = P.sel_cap, G = P.group;
   uint64_t* buf = (uint64_t*)lds;
@@ -166,7 +180,7 @@ __device__ void topk_epilogue(const FusedParams& P, u32x4* lds, const int64_t* r
                                                                           P.lds_keys_off);
   const int key_slots = P.key_cap / NW;
   const int64_t lo = ranges[0], hi = ranges[2 * NW - 1];
-  if (threadIdx.x == 0) P.wg_lo[blockIdx.x] = lo;
+  if (threadIdx.x == 0) P.wg_lo[wg] = lo;
   if (lo >= hi) return;
   const bool dense = P.cand_off == nullptr;
   // keys in one contiguous array from the first pair (as the scorer stored them)
@@ -176,12 +190,25 @@ __device__ void topk_epilogue(const FusedParams& P, u32x4* lds, const int64_t* r
     a0 = lo / P.n_docs;
     a1 = (hi - 1) / P.n_docs;
   } else {
-    a0 = wave_owner(P.cand_off, P.n_q, lo);
-    a1 = wave_owner(P.cand_off, P.n_q, hi - 1);
+    // the queries of the first and the last wave that had pairs
+    const int64_t* owners = ranges + 2 * NW;
+    a0 = a1 = -1;
+    for (int w = 0; w < NW; ++w) {
+      if (ranges[w] < ranges[NW + w]) {
+        if (a0 < 0) a0 = owners[w];
+        a1 = owners[NW + w];
+      }
+    }
   }
   for (int64_t a = a0; a <= a1; ++a) {
-    const int64_t s0 = dense ? a * P.n_docs : P.cand_off[a];
-    const int64_t s1 = dense ? s0 + P.n_docs : P.cand_off[a + 1];
+    int64_t s0 = lo, s1 = hi;  // (a query alone with the range needs no offsets)
+    if (dense) {
+      s0 = a * P.n_docs;
+      s1 = s0 + P.n_docs;
+    } else if (a0 != a1) {
+      s0 = P.cand_off[a];
+      s1 = P.cand_off[a + 1];
+    }
     const int64_t p0 = lo > s0 ? lo : s0, p1 = hi < s1 ? hi : s1;
     if (p0 >= p1) continue;
     for (int gq = 0; gq < G; ++gq) {
@@ -201,7 +228,7 @@ __device__ void topk_epilogue(const FusedParams& P, u32x4* lds, const int64_t* r
         return (wh - wl) * G <= key_slots ? lkeys[w * key_slots + (p - wl) * G + gq]
                                           : P.key_spill[p * G + gq];
       };
-      const int64_t slot = ((int64_t)blockIdx.x + a) * G + gq;
+      const int64_t slot = (wg + a) * G + gq;
       const int cnt = block_topk<1>(p1 - p0, k, hi32, lo32, hist, buf, cap, P.part_keys + slot * k);
       if (threadIdx.x == 0) P.part_cnt[slot] = (uint32_t)cnt;
     }
@@ -251,14 +278,66 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
   const int nch = P.nch;
   const int ncg = P.ncg;
 
-  const int64_t W = (int64_t)gridDim.x * NW;
-  const int64_t wg0 = (int64_t)blockIdx.x * NW;
-  const int64_t my_lo = uniform64(wave_range_begin(P, wg0 + wave, W));
-  const int64_t my_hi = uniform64(wave_range_begin(P, wg0 + wave + 1, W));
+  // The workgroup's place in the order of the work pairs. With several units
+  // (spread > 1) the workgroups of one document range follow each other on
+  // one XCD (workgroup b runs on XCD b mod 8), so a tile read for one unit is
+  // in that XCD's L2 for the others.
+  uint32_t wg = blockIdx.x;
+  if (P.spread > 1) {
+    const uint32_t s = wg >> 3, n = (uint32_t)P.spread;
+    wg = (s % n) * (gridDim.x / n) + (s / n) * 8 + (wg & 7);
+  }
+  const uint32_t W = gridDim.x * NW;
+  int64_t my_lo, my_hi;
+  wave_range(P, wg * NW + wave, W, my_lo, my_hi);
   // segments: the query-sized pieces of the workgroup's range (shared Q) or
   // of this wave's own range (per-wave Q)
-  int64_t pb = PERWAVE ? my_lo : uniform64(wave_range_begin(P, wg0, W));
-  const int64_t pe = PERWAVE ? my_hi : uniform64(wave_range_begin(P, wg0 + NW, W));
+  int64_t pb = my_lo, pe = my_hi;
+  if constexpr (!PERWAVE) {
+    int64_t unused;
+    wave_range(P, wg * NW, W, pb, unused);
+    wave_range(P, wg * NW + NW - 1, W, unused, pe);
+  }
+  // The first segment's query, its end, and the wave's first two documents
+  // are looked up together, by vector loads that are in flight at once: at
+  // the smallest sizes this chain of loads is most of a launch (scalar loads
+  // one after the other: the launch took 17.5 us, 15.6 this way, for 1,000
+  // candidates of one query with the top-100).
+  int64_t first_a = 0, first_end = 0;
+  int64_t first_s0 = 0, first_e0 = 0, first_s1 = 0, first_e1 = 0;
+  {
+    const bool any = my_lo < my_hi;
+    const int64_t fp = any ? (my_lo + (lane & 1) < my_hi ? my_lo + (lane & 1) : my_lo) : 0;
+    int64_t doc = 0;
+    if (P.cand_off != nullptr) {
+      if (any) doc = P.cand_ids[fp];
+      if (pb < pe) {
+        if (P.n_q < 64) {  // the offsets of all queries in the lanes
+          const int64_t off = P.cand_off[lane <= (int)P.n_q ? lane : (int)P.n_q];
+          const uint64_t past = __ballot(lane <= (int)P.n_q && off > pb);
+          const int end = past ? __ffsll((unsigned long long)past) - 1 : (int)P.n_q;
+          first_a = end - 1;
+          first_end = readlane64(off, end);
+        } else {
+          first_a = uniform64(wave_owner(P.cand_off, P.n_q, pb));
+          first_end = uniform64(P.cand_off[first_a + 1]);
+        }
+      }
+    } else {
+      first_a = P.n_units > 1 ? pb / P.n_docs : 0;
+      first_end = (first_a + 1) * P.n_docs;
+      if (any) doc = fp - (P.n_units > 1 ? my_lo / P.n_docs * P.n_docs : 0);
+      if (doc >= P.n_docs) doc = 0;  // the second pair is the next unit's first document
+    }
+    if (any) {
+      const int64_t ds = P.d_off[doc], de = P.d_off[doc + 1];
+      first_s0 = readlane64(ds, 0);
+      first_e0 = readlane64(de, 0);
+      first_s1 = readlane64(ds, 1);
+      first_e1 = readlane64(de, 1);
+    }
+  }
+  const int64_t first_pb = pb;
   // this wave's query operand in LDS (shared: the workgroup's copy)
   u32x4* qw = q_lds + (QM == Q_WAVE ? (size_t)wave * NQB * ncg * 64 : 0);
   // fused top-k: when the workgroup's whole range fits the LDS key slots,
@@ -285,13 +364,24 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
   }
 
   while (pb < pe) {
-    int64_t a, qend;  // a: the unit (with candidate lists: the query)
-    if (P.cand_off == nullptr) {
-      a = pb / P.n_docs;
-      qend = (a + 1) * P.n_docs;
-    } else {
-      a = uniform64(wave_owner(P.cand_off, P.n_q, pb));
-      qend = P.cand_off[a + 1];
+    int64_t a = first_a, qend = first_end;  // a: the unit (with candidate lists: the query)
+    if (pb != first_pb) {
+      if (P.cand_off == nullptr) {
+        a = pb / P.n_docs;
+        qend = (a + 1) * P.n_docs;
+      } else {
+        a = uniform64(wave_owner(P.cand_off, P.n_q, pb));
+        qend = P.cand_off[a + 1];
+      }
+    }
+    if (P.cand_off != nullptr) {
+      // (positions that no query owns, which only offsets breaking the
+      // contract leave, are passed over)
+      if (a < 0) {
+        pb = qend;
+        continue;
+      }
+      if (qend <= pb) break;
     }
     const int64_t se = qend < pe ? qend : pe;
     if constexpr (QM == Q_SHARED) {
@@ -313,21 +403,26 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     // (a unit holds at most 8 queries: the host never groups more)
     constexpr int NG = NQB < 8 ? NQB : 8;
     const int bpq = P.bpq;
+    // the unit's query offsets, one per lane (past the last query: its end)
+    const int64_t qi = a * P.group + (lane < 15 ? lane : 15);
+    const int64_t qo = P.q_off[qi < P.n_q ? qi : P.n_q];
     uint32_t qmask = 0;
 #pragma unroll
     for (int gq = 0; gq < NG; ++gq) {
-      const int64_t qa = a * P.group + gq;
-      if (gq < P.group && qa < P.n_q) {
-        const int n = (int)(P.q_off[qa + 1] - P.q_off[qa]);
+      if (gq < P.group && a * P.group + gq < P.n_q) {
+        const int n = (int)(readlane64(qo, gq + 1) - readlane64(qo, gq));
         qmask |= 1u << gq;
         if (n > 0) qmask |= 1u << (8 + gq);
         if (n > bpq * 16) qmask |= 1u << (16 + gq);
       }
     }
-    qmask = __builtin_amdgcn_readfirstlane(qmask);
 
     int64_t lo = my_lo > pb ? my_lo : pb;
     const int64_t hi = my_hi < se ? my_hi : se;
+    if (P.topk_k > 0 && P.cand_off != nullptr && lo < hi && lane == 0) {
+      if (lo == my_lo) ranges[2 * NW + wave] = a;
+      if (hi == my_hi) ranges[3 * NW + wave] = a;
+    }
     const int64_t pair_base = (P.cand_off == nullptr) ? a * P.n_docs : 0;
 
     // Query operand registers (one d-chunk, loaded by the wave itself) and
@@ -340,8 +435,8 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
       int64_t q0 = 0;
       int nq = 0;
       if (qa >= 0) {
-        q0 = P.q_off[qa];
-        nq = (int)(P.q_off[qa + 1] - q0);
+        q0 = readlane64(qo, nb / bpq);
+        nq = (int)(readlane64(qo, nb / bpq + 1) - q0);
       }
       const int row = (nb % bpq) * 16 + r;
       if constexpr (QREG) {
@@ -402,6 +497,27 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
       }
     };
 
+    // Lane 16 q of v holds query q0 + q's score of work pair pp, for each set
+    // bit q of rows: one store for all of them.
+    auto store_rows = [&](int64_t pp, int q0, int rows, float v) {
+      const int gq = q0 + g;
+      if (r == 0 && ((rows >> g) & 1) && ((qmask >> gq) & 1u)) {
+        if ((qmask >> (16 + gq)) & 1u) v = __builtin_bit_cast(float, 0x7fc00000u);
+        if (P.topk_k > 0) {
+          const int64_t e = pp * P.group + gq;
+          const uint32_t key = topk_detail::score_key(v);
+          if (keys_contig)
+            wg_keys[e - wg_lo * P.group] = key;
+          else if (keys_in_lds)
+            wave_keys[e - my_lo * P.group] = key;
+          else
+            P.key_spill[e] = key;
+        } else {
+          P.scores[pp + sbase + (int64_t)gq * P.n_docs] = v;
+        }
+      }
+    };
+
     // ---- prefetch cursor over the (pair, tile, chunk) steps of [lo, hi) ----
     // Document offsets (and candidate ids) are read with scalar loads from
     // the constant address space, one document ahead: they are counted by
@@ -422,48 +538,71 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     // the same MFMA output either way, so the scores are the same bits.
     constexpr bool PACK = DT == DT_F32 && QREG && RT == 16;
     const bool pack = PACK && !has_cand;
-    int64_t cp = lo;  // cursor pair
+    // positions relative to lo: a segment is part of one unit's documents (or
+    // one query's candidates), below 2^31 of them
+    int ci = 0;
+    const int cn = (int)(hi - lo);
     int64_t ct0 = 0;
+    const char* ctp = nullptr;  // the document's first row
     int cnd = 0, ctile = 0, cchunk = 0, cbase = 0;
-    int64_t nx_s = 0, nx_e = 0;  // offsets of pair cp + 1 (raw)
-    int nx2_id = 0;              // candidate id of pair cp + 2
-    if (cp < hi) {
-      int id0 = has_cand ? sload_i32(P.cand_ids, cp) : 0;
-      int64_t b0 = doc_of(cp, id0);
-      ct0 = sload_i64(doff, b0);
-      cnd = (int)(sload_i64(doff, b0 + 1) - ct0);
-      if (cp + 1 < hi) {
-        int id1 = has_cand ? sload_i32(P.cand_ids, cp + 1) : 0;
-        int64_t b1 = doc_of(cp + 1, id1);
-        nx_s = sload_i64(doff, b1);
-        nx_e = sload_i64(doff, b1 + 1);
+    int64_t nx_s = 0, nx_e = 0;  // offsets of pair ci + 1 (raw)
+    int nx2_id = 0;              // candidate id of pair ci + 2
+    if (cn > 0) {
+      if (lo == my_lo) {
+        ct0 = first_s0;
+        cnd = (int)(first_e0 - first_s0);
+        nx_s = first_s1;
+        nx_e = first_e1;
+      } else {
+        const int64_t b0 = doc_of(lo, has_cand ? sload_i32(P.cand_ids, lo) : 0);
+        ct0 = sload_i64(doff, b0);
+        cnd = (int)(sload_i64(doff, b0 + 1) - ct0);
+        if (cn > 1) {
+          const int64_t b1 = doc_of(lo + 1, has_cand ? sload_i32(P.cand_ids, lo + 1) : 0);
+          nx_s = sload_i64(doff, b1);
+          nx_e = sload_i64(doff, b1 + 1);
+        }
       }
-      if (has_cand && cp + 2 < hi) nx2_id = sload_i32(P.cand_ids, cp + 2);
+      ctp = P.d_tok + ct0 * P.row_bytes;
+      if (has_cand && cn > 2) nx2_id = sload_i32(P.cand_ids, lo + 2);
     }
 
     auto next_pair = [&]() {
-      ++cp;
+      ++ci;
       ctile = 0;
       cchunk = 0;
       cbase = 0;
       ct0 = nx_s;
+      ctp = P.d_tok + ct0 * P.row_bytes;
       cnd = (int)(nx_e - nx_s);
-      if (cp + 1 < hi) {
-        int64_t b1 = doc_of(cp + 1, nx2_id);
+      if (ci + 1 < cn) {
+        const int64_t b1 = doc_of(lo + ci + 1, nx2_id);
         nx_s = sload_i64(doff, b1);
         nx_e = sload_i64(doff, b1 + 1);
-        if (has_cand && cp + 2 < hi) nx2_id = sload_i32(P.cand_ids, cp + 2);
+        if (has_cand && ci + 2 < cn) nx2_id = sload_i32(P.cand_ids, lo + ci + 2);
       }
     };
 
     u32x4 buf[STAGE ? 1 : PF][NL];
     int bsc[PF][SUB];
     int flags[PF];
-    int64_t fp[PF];
     constexpr int Q_COPIES = QM == Q_SHARED ? 1 : (QM == Q_WAVE ? NW : 0);
     char* ring =
         (char*)q_lds + (size_t)Q_COPIES * NQB * 16 * ncg * 64 + (size_t)wave * PF * TILE;
     auto swz = [](int row) { return (row / SWD) & (SW - 1); };
+    // this lane's row and column offsets of each load of a step (one chunk:
+    // the same for every step)
+    int off_row[STAGE ? NLS : 1], off_col[STAGE ? NLS : 1];
+    if constexpr (STAGE) {
+#pragma unroll
+      for (int w = 0; w < NLS; ++w) {
+        const int ch = 64 * w + lane;  // LDS slot of this lane's 16 bytes
+        const int rho = ch / CPR, p = ch % CPR;
+        const int col = (p ^ swz(rho)) * 16;
+        off_row[w] = rho * P.row_bytes;
+        off_col[w] = QREG && col > P.row_bytes - 16 ? P.row_bytes - 16 : col;
+      }
+    }
 
     // Every fill issues exactly NL (+1 for FP8) loads, from a harmless address
     // when there is nothing left to load, so the compiler's vmcnt accounting
@@ -473,24 +612,26 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     auto fill = [&](const int s) {
       int f = 0;
       const char* base = zrow;
-      const bool live = cp < hi && cnd != 0;
+      const bool live = ci < cn && cnd != 0;
       const int rb = (PACK ? cbase : 0) + ctile * RT;  // first document row of this step
       // packed: this document's rows in the tile (1-15), the rest the next one's
       int ra = 0;
-      if (PACK && pack && live && rb + RT > cnd && cp + 1 < hi && nx_e - nx_s > RT - (cnd - rb))
+      if (PACK && pack && live && rb + RT > cnd && ci + 1 < cn && nx_e - nx_s > RT - (cnd - rb))
         ra = cnd - rb;
       // largest in-row offset from this step's chunk start (idle: none needed)
       const int cmax = live ? P.row_bytes - 16 - cchunk * CB : CB;
-      fp[s] = cp;
-      if (cp < hi) {
+      if (ci < cn) {
         if (cnd == 0) {
           f = F_VALID | F_EMPTY;
         } else {
-          int row = rb + r;
-          if (ra == 0) row = row < cnd ? row : cnd - 1;
-          base = P.d_tok + (ct0 + row) * P.row_bytes + cchunk * CB;
-          f = F_VALID | (cchunk == 0 ? F_TFIRST : 0) | (cchunk << 8);
-          if (cchunk == nch - 1) {
+          if constexpr (!STAGE) {
+            int row = rb + r;
+            if (ra == 0) row = row < cnd ? row : cnd - 1;
+            base = ctp + (int64_t)row * P.row_bytes + cchunk * CB;
+          }
+          f = F_VALID;
+          if (!QREG) f |= (cchunk == 0 ? F_TFIRST : 0) | (cchunk << 8);
+          if (QREG || cchunk == nch - 1) {
             f |= F_TLAST;
             if (rb + RT >= cnd) f |= F_DLAST;
             if (ra != 0) f |= F_SPLIT | (ra << SPLIT_SHIFT);
@@ -501,19 +642,16 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
         // uniform tile base + per-lane 32-bit offset; an idle fill reads row
         // 0 of the zero block (offsets stay below CB <= 1 KiB)
         const char* tb = zrow;
-        int lim = 0;
+        int lim = 0;  // last row of the tile that exists, as an offset
         if (live) {
-          tb = P.d_tok + (ct0 + rb) * P.row_bytes + cchunk * CB;
-          lim = ra != 0 ? RT - 1 : cnd - 1 - rb;
+          tb = ctp + (int64_t)rb * P.row_bytes + (QREG ? 0 : cchunk * CB);
+          lim = ((ra != 0 || cnd - rb >= RT) ? RT - 1 : cnd - 1 - rb) * P.row_bytes;
         }
         char* slot = ring + s * TILE;
 #pragma unroll
         for (int w = 0; w < NLS; ++w) {
-          const int ch = 64 * w + lane;  // LDS slot of this lane's 16 bytes
-          const int rho = ch / CPR, p = ch % CPR;
-          const int col = (p ^ swz(rho)) * 16;
-          const unsigned off =
-              (unsigned)((rho < lim ? rho : lim) * P.row_bytes + (col < cmax ? col : cmax));
+          const int col = QREG || off_col[w] < cmax ? off_col[w] : cmax;
+          const unsigned off = (unsigned)((off_row[w] < lim ? off_row[w] : lim) + col);
           __builtin_amdgcn_global_load_lds((const void*)(tb + off),
                                            (__attribute__((address_space(3))) void*)(slot + w * 1024),
                                            16, 0, 2 /* non-temporal */);
@@ -540,10 +678,10 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
         }
       }
       flags[s] = f;
-      if (cp < hi) {
+      if (ci < cn) {
         if (cnd == 0) {
           next_pair();
-        } else if (++cchunk == nch) {
+        } else if (QREG || ++cchunk == nch) {
           cchunk = 0;
           ++ctile;
           if (ra != 0) {
@@ -569,7 +707,46 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     // block), sum over its blocks and then its 16 columns (four DPP
     // rotations); register to register, so a wave alone on its SIMD keeps
     // issuing (with LDS shuffles here a launch measured up to 7% slower)
+    // Several queries in a unit: their blocks share the swaps, each
+    // exchange finishing a step of the max of two blocks, until the four lane
+    // rows hold four blocks, which one rotation sum then adds up together:
+    // four 32-token queries take 6 swaps, 4 rotations and one store instead of
+    // 16, 16 and four. The sums add the same values in the same order.
     auto finalize = [&](int64_t pp) {
+      auto reset = [&]() {
+#pragma unroll
+        for (int nb = 0; nb < NQB; ++nb) mx[nb] = -__builtin_inff();
+      };
+      if constexpr (NQB == 8) {
+        if (bpq == 2) {
+          const float x = max_rows_of4(mx[0], mx[2], mx[4], mx[6]);
+          const float y = max_rows_of4(mx[1], mx[3], mx[5], mx[7]);
+          store_rows(pp, 0, 0xF, row_sum16((0.f + x) + y));
+          return reset();
+        }
+        if (bpq == 1) {
+          const float x = max_rows_of4(mx[0], mx[1], mx[2], mx[3]);
+          const float y = max_rows_of4(mx[4], mx[5], mx[6], mx[7]);
+          store_rows(pp, 0, 0xF, row_sum16(0.f + x));
+          store_rows(pp, 4, 0xF, row_sum16(0.f + y));
+          return reset();
+        }
+      }
+      if constexpr (NQB == 4) {
+        if (bpq == 2) {
+          const float x = max_row_pairs(max_halves_of2(mx[0], mx[2]));
+          const float y = max_row_pairs(max_halves_of2(mx[1], mx[3]));
+          // rows 0 and 2: queries 0 and 1
+          const float t = row_sum16((0.f + x) + y);
+          store_rows(pp, 0, 0x1, t);
+          store_rows(pp, -1, 0x4, t);
+          return reset();
+        }
+        if (bpq == 1) {
+          store_rows(pp, 0, 0xF, row_sum16(0.f + max_rows_of4(mx[0], mx[1], mx[2], mx[3])));
+          return reset();
+        }
+      }
       float tot = 0.f;
 #pragma unroll
       for (int nb = 0; nb < NQB; ++nb) {
@@ -605,26 +782,29 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     };
     // after a step: a document that ends in it is scored; a split tile's
     // rows of the next document become that document's running maxima
-    auto end_step = [&](const int fl, const int64_t pp) {
+    int64_t pp = lo;  // work pair being scored (pairs are scored in order)
+    auto end_step = [&](const int fl) {
       if (PACK && (fl & F_SPLIT)) {
         finalize(pp);
+        ++pp;
 #pragma unroll
         for (int nb = 0; nb < NQB; ++nb) mx[nb] = mxn[nb];
       } else if (fl & F_DLAST) {
         finalize(pp);
+        ++pp;
       }
+    };
+    auto empty_doc = [&]() {
+      for (int gq = 0; gq < NG; ++gq)
+        if ((qmask >> gq) & 1u)
+          store(pp, gq, ((qmask >> (8 + gq)) & 1u) ? -__builtin_inff() : 0.f);
+      ++pp;
     };
 
     auto consume = [&](const int s) {
       const int fl = flags[s], sc = bsc[s][0];
-      const int64_t pp = fp[s];
       if (!(fl & F_VALID)) return;
-      if (fl & F_EMPTY) {
-        for (int gq = 0; gq < NG; ++gq)
-          if ((qmask >> gq) & 1u)
-            store(pp, gq, ((qmask >> (8 + gq)) & 1u) ? -__builtin_inff() : 0.f);
-        return;
-      }
+      if (fl & F_EMPTY) return empty_doc();
       u32x4 bb[NL];
       if constexpr (STAGE) {
         // every later fill issued LOADS_PER_FILL vector memory operations
@@ -678,7 +858,7 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
           }
         }
       }
-      end_step(fl, pp);
+      end_step(fl);
     };
 
     // The arithmetic-heaviest forms (eight query blocks over LDS-staged
@@ -692,9 +872,8 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     // is as fast or faster).
     constexpr bool EARLY = STAGE && QREG && RT == 16 &&
                            ((NQB == 8 && (DT == DT_F16 || DT == DT_BF16)) || DT == DT_F32);
-    auto take = [&](const int s, u32x4 (&bb)[NL], int& fl, int64_t& pp) {
+    auto take = [&](const int s, u32x4 (&bb)[NL], int& fl) {
       fl = flags[s];
-      pp = fp[s];
       // every later fill issued LOADS_PER_FILL vector memory operations; the
       // wait is on every path, so the compiler's own accounting also sees the
       // segment's query operand loads complete before any MFMA
@@ -707,20 +886,15 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
       // the slot's LDS reads complete before its refill can land
       __builtin_amdgcn_s_waitcnt(lgkmcnt0_imm());
     };
-    auto compute = [&](const u32x4 (&bb)[NL], const int fl, const int64_t pp) {
+    auto compute = [&](const u32x4 (&bb)[NL], const int fl) {
       if (!(fl & F_VALID)) return;
-      if (fl & F_EMPTY) {
-        for (int gq = 0; gq < NG; ++gq)
-          if ((qmask >> gq) & 1u)
-            store(pp, gq, ((qmask >> (8 + gq)) & 1u) ? -__builtin_inff() : 0.f);
-        return;
-      }
+      if (fl & F_EMPTY) return empty_doc();
       if constexpr (EARLY) {
 #pragma unroll
         for (int nb = 0; nb < NQB; ++nb)
           tile_max(nb, mma_step<DT, NL>(f32x4{0.f, 0.f, 0.f, 0.f}, bb, qreg[nb], 127, 127), fl);
       }
-      end_step(fl, pp);
+      end_step(fl);
     };
 
 #pragma unroll
@@ -733,10 +907,9 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
           if constexpr (EARLY) {
             u32x4 bb[NL];
             int fl;
-            int64_t pp;
-            take(s, bb, fl, pp);
+            take(s, bb, fl);
             fill(s);
-            compute(bb, fl, pp);
+            compute(bb, fl);
           } else {
             consume(s);
             fill(s);
@@ -759,7 +932,7 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     // once every wave is done the query operand and ring area is free for
     // the selection
     __syncthreads();
-    topk_epilogue<NW>(P, q_lds, ranges);
+    topk_epilogue<NW>(P, wg, q_lds, ranges);
   }
 }
 

@@ -35,6 +35,10 @@ struct FusedParams {
   int32_t ncg;
   int64_t n_units;   // ceil(n_q / group)
   int64_t n_upairs;  // work pairs: n_units * n_docs, or the candidate count
+  // Total of the quantity the waves share equally (document tokens of every
+  // unit, or work pairs), divided by the number of waves of the launch.
+  int64_t share_q, share_r;
+  int32_t spread;  // > 1: the units, their workgroups interleaved (grid % (8 spread) == 0)
   // Fused top-k (topk_k > 0): a score is not stored; its ranking key goes to
   // LDS at byte lds_keys_off of the dynamic LDS (key_cap slots): one array
   // indexed from the workgroup's first pair when its whole range fits, else
@@ -47,7 +51,7 @@ struct FusedParams {
   int32_t topk_k;
   int32_t sel_cap;       // sort-buffer keys of the selection (power of two >= max(k, 64))
   int32_t key_cap;       // LDS key slots of the workgroup (a multiple of its wave count)
-  int32_t lds_keys_off;  // bytes; the wave ranges follow the key slots
+  int32_t lds_keys_off;  // bytes; the wave ranges and owners follow the key slots
   uint32_t* key_spill;   // [n_upairs * group]
   int64_t* wg_lo;        // [grid]
   uint64_t* part_keys;   // [(grid + n_units) * group * topk_k]

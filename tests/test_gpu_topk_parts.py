@@ -4,6 +4,7 @@ ties, NaN and infinities, and merges whose answer sits in one part. Every
 result must equal a sort of the same values on the CPU."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2606_26439_amd as M
 import workloads as W
@@ -90,3 +91,27 @@ def test_score_topk_of_candidate_lists(dtype, dim, k):
     sc = M.score(Q, D, cand).cpu().numpy()
     ts, ti = M.score_topk(Q, D, k, cand)
     _check(ts, ti, sc, c_off, k, ids)
+
+
+@pytest.mark.parametrize("n_q", [8, 14, 16, 24])
+@pytest.mark.parametrize("k", [0, 10, 1000])
+def test_units_interleaved_over_workgroups(n_q, k):
+    # several units of four 32-token queries over one document range: each
+    # query's scores and ranking equal its own call's
+    g = W.rng(n_q)
+    lens = g.integers(0, 12, size=6001)
+    d_off = W.offsets_from_lengths(lens)
+    d = W.unit_tokens(int(d_off[-1]), 128, g)
+    q_off = W.offsets_from_lengths([32] * n_q)
+    q = W.unit_tokens(32 * n_q, 128, g)
+    Q, D = device_tokens(q, q_off, "f16"), device_tokens(d, d_off, "f16")
+    one = [device_tokens(q[32 * a:32 * a + 32], [0, 32], "f16") for a in range(n_q)]
+    if k == 0:
+        got = M.score(Q, D)
+        for a in range(n_q):
+            assert torch.equal(got[a * 6001:(a + 1) * 6001], M.score(one[a], D)), a
+        return
+    ts, ti = M.score_topk(Q, D, k)
+    for a in range(n_q):
+        sc = M.score(one[a], D).cpu().numpy()
+        _check(ts[a:a + 1], ti[a:a + 1], sc, [0, 6001], k)
