@@ -148,8 +148,11 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # the current stream's handle without building a Stream object (2.9 us of
+    # the host time of every call)
+    if stream is None:
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 class Tokens:
@@ -276,14 +279,13 @@ def score_topk(q: Tokens, d: Tokens, k: int, cand: Candidates = None, workspace=
     if out is None:
         out = (torch.empty((q.n_sets, k), dtype=torch.float32, device=dev),
                torch.empty((q.n_sets, k), dtype=torch.int32, device=dev))
-    if workspace is None:
-        workspace = torch.empty(max(score_topk_workspace_bytes(q, d, k, cand), 1),
-                                dtype=torch.uint8, device=dev)
     qc, dc = q.csr(), d.csr()
     cc = cand.c() if cand is not None else None
-    _check(lib().maxsim_score_topk(ctypes.byref(qc), ctypes.byref(dc),
-                                   ctypes.byref(cc) if cc is not None else None, k,
-                                   _ptr(out[0]), _ptr(out[1]), _ptr(workspace),
+    qp, dp, cp = ctypes.byref(qc), ctypes.byref(dc), ctypes.byref(cc) if cc is not None else None
+    if workspace is None:
+        need = int(lib().maxsim_score_topk_workspace_size(qp, dp, cp, k))
+        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+    _check(lib().maxsim_score_topk(qp, dp, cp, k, _ptr(out[0]), _ptr(out[1]), _ptr(workspace),
                                    workspace.numel(), _stream(stream)))
     return out
 
