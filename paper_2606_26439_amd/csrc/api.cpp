@@ -92,8 +92,9 @@ DevInfo device_info() {
 // ---------------------------------------------------------------- tuning --
 
 // units: 0 when a launch has one query unit, 1 when several units re-read the
-// same documents (those come from the caches then, not from HBM). A cache
-// entry without it holds for both until one with it says otherwise.
+// same documents (those come from the caches then, not from HBM), 2 with
+// candidate lists (scattered documents, often only a few for each wave). A
+// cache entry without it holds for all until one with it says otherwise.
 struct TuneKey {
   int dt, dim, nqb, units;
   bool operator<(const TuneKey& o) const {
@@ -193,11 +194,16 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
   const int qrow_bytes = nch * pl.dch * esize(q->dtype);
   int group = 1;
   if (!cand && group_queries) {
-    // in LDS (d beyond one chunk) the grouped query blocks leave at least
-    // half of it to the staging ring
+    // in LDS (d beyond one chunk) the grouped query blocks take up to four
+    // fifths of it: a document read saved is worth more than the staging ring
+    // (d = 768, 32-token queries: two at once 1235 -> 834 us over 50K documents
+    // of 70 tokens, sixteen 8.56 -> 4.75 ms; d = 1024, four 1895 -> 1145 us).
+    // Only half of it from 2^23 pairs on: a group's top-k parts add up, and
+    // what fits the fixed scratch of maxsim_score_topk_noalloc stays within it.
     const int cap = (pl.qreg && esize(q->dtype) <= 2) ? 8 : 4;
+    const size_t lds = device_info().max_lds, room = n_pairs < (1 << 23) ? lds / 5 * 4 : lds / 2;
     auto fits = [&](int gr) {
-      return pl.qreg || (size_t)gr * bpq * 16 * qrow_bytes <= device_info().max_lds / 2;
+      return pl.qreg || (size_t)gr * bpq * 16 * qrow_bytes <= room;
     };
     while (group * 2 * bpq <= cap && group * 2 <= q->n_sets && fits(group * 2)) group *= 2;
   }
@@ -231,71 +237,74 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
   return MAXSIM_OK;
 }
 
-// Untuned keys, by what was measured on MI355X (32-token queries over ragged
-// documents unless said):
-//   * the register-direct form with three steps in flight and eight waves
-//     where documents do not come from HBM at one read each: several units of
-//     eight query blocks (16 queries, 100K documents: 0.94 against 1.03 ms
-//     staged; one unit: 2.92 against 2.87, staged), chunk rows of at most 128
-//     bytes against four or more blocks (FP8 d = 128, four queries: 109
-//     against 130 us), 64-wide chunks of a d that is no multiple of 128
-//     (FP16 d = 400: 629 against 872 us);
-//   * FP32: staged, eight waves (two-query units 1.92 against 2.13 ms) where
-//     the ring fits, else register-direct;
-//   * else staged when the ring fits beside the query block.
-FusedCfg default_cfg(const FusedPlan& pl, int units) {
+// LDS that a launch with the top-k epilogue keeps for keys and wave ranges.
+constexpr size_t TOPK_LDS = 4096;
+
+// Untuned keys: eight waves, the shape by what was measured on MI355X (us of a
+// pass: 2 GB of ragged documents scored by one query / 0.5 GB of candidates of
+// eight queries, unless said; Q blocks: 16 query tokens each):
+//   * 64-wide chunks (d above 128, no multiple of it): register-direct, three
+//     steps in flight (FP16 d = 400, two blocks 402 / 179 against 448 / 196
+//     staged);
+//   * FP32: register-direct, two steps (d = 64, four blocks 628 / 226 against
+//     644 / 228); staged for one block without candidates (d = 256 343 against
+//     357); four waves where candidates give a wave at most a document (1,000
+//     of a 64-token query: 60 against 82);
+//   * eight blocks: staged with two steps for one unit (2.87 against 2.92 ms
+//     over 1M documents), direct for several, whose documents come from the
+//     caches (16 queries, 100K documents: 0.94 against 1.03 ms), and for FP8
+//     (four queries 109 against 130);
+//   * FP8: staged, three steps (d = 256, two blocks 326 against 359 direct);
+//     direct with candidates (four blocks 149 against 183) and at d <= 64 with
+//     four blocks (409 against 427);
+//   * FP16 and BF16: staged, two steps (d = 256, four blocks 323 against 356
+//     direct, 405 with four waves); direct where four blocks in LDS meet
+//     candidates (d = 256 140 against 169) or several units (16 queries,
+//     d = 768: 4.75 against 5.21 ms);
+//   * direct wherever the ring does not fit beside the query blocks.
+FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
+  const DevInfo di = device_info();
   const int esz = esize(pl.dt);
-  const size_t q_lds = pl.qreg ? 0 : pl.lds, max_lds = device_info().max_lds;
-  auto ring = [&](int nw, int pf) { return q_lds + (size_t)nw * pf * 16 * pl.dch * esz; };
+  const bool cand = units == 2, chunk64 = pl.dch == 64 && pl.P.nch > 1;
   FusedCfg c;
-  c.nw = 4;
+  c.nw = 8;
   c.wg_per_cu = 0;
   if (pl.dt == MAXSIM_F32) {
-    c.pf = 2;
-    c.stage = 0;
-    if (pl.qreg && ring(8, 2) <= max_lds) {
-      c.nw = 8;
-      c.wg_per_cu = 1;
-      c.stage = 1;
-    }
-    return c;
-  }
-  if ((pl.dch == 64 && pl.P.nch > 1) || (pl.qreg && pl.nqb >= 4 && pl.dch * esz <= 128) ||
-      (pl.nqb == 8 && units)) {
+    c.pf = chunk64 ? 3 : 2;
+    c.stage = !chunk64 && !cand && pl.nqb == 1;
+    if (cand && pl.n_pairs <= 8 * (int64_t)di.cus) c.nw = 4;
+  } else if (chunk64) {
     c.pf = 3;
-    c.nw = 8;
-    c.wg_per_cu = pl.nqb == 8 ? 2 : 1;
     c.stage = 0;
-    return c;
-  }
-  if (pl.nqb == 8) {
-    c.pf = 2;
-    c.nw = 8;
+  } else if (pl.nqb == 8) {
+    c.stage = !units && pl.dt != MAXSIM_F8E4M3;
+    c.pf = c.stage ? 2 : 3;
     c.wg_per_cu = 2;
-    c.stage = 1;
-    return c;
+  } else if (pl.dt == MAXSIM_F8E4M3) {
+    c.pf = 3;
+    c.stage = !cand && !(pl.nqb == 4 && pl.dch == 64);
+  } else {
+    c.stage = pl.qreg || pl.nqb < 4 || !units;
+    c.pf = c.stage || cand ? 2 : 4;
   }
-  c.pf = 3;
-  c.stage = 1;
-  if (ring(c.nw, c.pf) > max_lds) {
-    c.pf = 4;
-    c.stage = 0;
-  }
+  // (a 256-wide chunk is taken as two of 128 where only their ring fits)
+  const size_t q_lds = (pl.qreg ? 0 : pl.lds) + (topk ? TOPK_LDS : 0);
+  if (q_lds + (size_t)c.nw * c.pf * 16 * std::min(pl.dch, 128) * esz > di.max_lds) c.stage = 0;
   return c;
 }
 
 TuneKey tune_key(const FusedPlan& pl) {
-  return {pl.dt, pl.P.dim, pl.nqb, !pl.P.cand_off && pl.P.n_units > 1 ? 1 : 0};
+  return {pl.dt, pl.P.dim, pl.nqb, pl.P.cand_off ? 2 : pl.P.n_units > 1 ? 1 : 0};
 }
 
-FusedCfg lookup_cfg(const FusedPlan& pl) {
+FusedCfg lookup_cfg(const FusedPlan& pl, bool topk = false) {
   const TuneKey k = tune_key(pl);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(k);
     if (it != g_tuned.end()) return it->second;
   }
-  return default_cfg(pl, k.units);
+  return default_cfg(pl, k.units, topk);
 }
 
 // A fused launch ready to go: kernel, parameters, dynamic LDS and grid.
@@ -320,8 +329,8 @@ maxsim_status prepare_fused(const FusedPlan& pl, const FusedCfg& cfg, int topk_k
   // ring fits beside one copy of the query blocks; else 128-wide
   FusedParams P = pl.P;
   int dch = pl.dch;
-  if (dch == 256 && (!cfg.stage || pl.lds + (size_t)cfg.nw * cfg.pf * 16 * 256 * esize(pl.dt) >
-                                       di.max_lds)) {
+  if (dch == 256 && (!cfg.stage || pl.lds + (size_t)cfg.nw * cfg.pf * 16 * 256 * esize(pl.dt) +
+                                           (topk_k > 0 ? TOPK_LDS : 0) > di.max_lds)) {
     dch = 128;  // d is a multiple of 256 here: the same padded row
     P.nch = P.dim / dch;
   }
@@ -536,7 +545,7 @@ maxsim_status plan_score_topk(const maxsim_csr* q, const maxsim_csr* d,
   maxsim_status st = plan_fused(q, d, cand, nullptr, pl, true, /*need_scores=*/false);
   if (st) return st;
   if (pl.n_pairs > 0) {
-    FusedCfg cfg = lookup_cfg(pl);
+    FusedCfg cfg = lookup_cfg(pl, true);
     if ((st = prepare_fused(pl, cfg, k, L))) return st;
   } else {
     L.P = pl.P;
@@ -1399,13 +1408,10 @@ maxsim_status maxsim_load_tune_cache(const char* path) {
       if (!json_int(obj.c_str(), "rows", c.rows)) c.rows = 16;
       if ((c.pf >= 2 && c.pf <= 4) && (c.nw == 4 || c.nw == 8) && (c.stage == 0 || c.stage == 1) &&
           (c.rows == 16 || c.rows == 32)) {
-        const bool both = !json_int(obj.c_str(), "units", k.units);
-        if (both) k.units = 0;
-        if (k.units == 0 || k.units == 1) g_tuned[k] = c;
-        if (both) {
-          k.units = 1;
-          g_tuned[k] = c;
-        }
+        int units = -1;  // every value
+        const bool one = json_int(obj.c_str(), "units", units);
+        for (k.units = 0; k.units < 3; ++k.units)
+          if (!one || k.units == units) g_tuned[k] = c;
       }
     }
     pos = end;
@@ -1474,7 +1480,7 @@ maxsim_status maxsim_autotune(const maxsim_csr* queries, const maxsim_csr* docs,
                     std::to_string(queries->dim) + ",\"nqb\":" + std::to_string(pl.nqb) +
                     ",\"trials\":[";
   float best_ms = 1e30f;
-  FusedCfg best = default_cfg(pl, tune_key(pl).units);
+  FusedCfg best = default_cfg(pl, tune_key(pl).units, false);
   bool first = true;
   for (const FusedCfg& c : space) {
     if (run_fused(pl, c, s)) continue;  // warm-up (also skips shapes that do not fit)
