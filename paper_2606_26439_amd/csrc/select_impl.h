@@ -6,8 +6,8 @@
 // the low 32 bits are ~id. Key 0 never belongs to a real entry (ids are below
 // 2^31, so ~id >= 2^31) and serves as padding that ranks below everything.
 //
-// block_topk() finds the k largest keys of n entries, enumerated by a
-// callable get(i), with a radix select: starting from the bits all keys
+// block_topk() finds the k largest keys of n entries, enumerated by callables
+// of their high and low words, with a radix select: starting from the bits all keys
 // share, 12-bit digits fix a key prefix until the entries above the prefix
 // plus the entries on it fit the sort buffer; those are collected and sorted
 // by a bitonic network. Integer

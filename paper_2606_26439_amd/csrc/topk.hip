@@ -457,6 +457,7 @@ hipError_t launch_topk_merge(const MergeParams& M, hipStream_t st) {
 namespace {
 
 constexpr int PART_SCORES = 6144;  // score keys of a share kept in LDS
+constexpr int PART_AIM = 2048;     // a share of an average segment
 
 // Parts of a segment in its workspace: np counts, then np times k keys.
 __device__ __forceinline__ uint32_t* part_counts(void* ws, int64_t s) { return (uint32_t*)seg_ws(ws, s); }
@@ -527,12 +528,13 @@ hipError_t launch_topk(const float* scores, const int64_t* seg_off, int64_t n_se
                        hipStream_t st) {
   if (n_seg == 0) return hipSuccess;
   const int64_t avg = n_total / n_seg;
-  // Shares of about PART_SCORES scores, as many as the workspace has room for
-  // the parts of; where that makes a share longer than four times that
+  // Shares of about PART_AIM scores (so that a segment three times the average
+  // still has its shares in LDS), as many as the workspace has room for the
+  // parts of; where that makes a share longer than four times that
   // (k = 1000 from about 220K scores a segment on), the histogram launches.
   // Eight segments of 1K to 94K scores, k = 100: 32 us against 65.
   const int64_t np =
-      std::min<int64_t>(std::max<int64_t>(1, (avg + PART_SCORES - 1) / PART_SCORES),
+      std::min<int64_t>(std::max<int64_t>(1, (avg + PART_AIM - 1) / PART_AIM),
                         std::min(max_parts(k), MERGE_MAX_GRID));
   if (avg <= np * PART_SCORES * 4) {
     hipLaunchKernelGGL(topk_part_kernel, dim3((unsigned)np, (unsigned)n_seg), dim3(MERGE_THREADS),
