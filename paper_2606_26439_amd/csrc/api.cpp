@@ -169,9 +169,14 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
   }
   if (n_pairs > 0 && !scores && need_scores) return fail(MAXSIM_EINVAL, "scores is NULL");
   pl.dt = q->dtype;
-  // d-chunk width: 128 (the paper's dimension tiling), 64 when d > 128 is not
-  // a multiple of 128, and 256 for 1- and 2-byte rows of d >= 256 (same k
-  // order, so the same bits; each row read becomes 512 contiguous bytes). A d
+  // d-chunk width: 128 (the paper's dimension tiling), 64 for FP32 when
+  // d > 128 is not a multiple of 128, and 256 for 1- and 2-byte rows of a d
+  // that is a multiple of 256 (same k order, so the same bits; each row read
+  // becomes 512 contiguous bytes). FP32 is bound by its matrix rate, so there
+  // the zeros of half a chunk cost more than the wider reads give (d = 144,
+  // two queries 638 against 802 us); the narrow types are not (1.5 GB of
+  // documents, one query: FP16 d = 144 302 against 337 us with 64, d = 400 302
+  // against 332; FP8 d = 400 326 against 422, d = 144 336 against 393). A d
   // that is not a multiple of the chunk is zero-extended to whole chunks
   // inside the kernel: the query operand's columns past d are zero and the
   // document columns past d are read from inside the row, so they add exact
@@ -179,7 +184,7 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
   if (q->dim <= 128)
     pl.dch = q->dim <= 64 ? 64 : 128;
   else
-    pl.dch = (q->dim % 128 == 0) ? 128 : 64;
+    pl.dch = (q->dim % 128 == 0 || esize(q->dtype) <= 2) ? 128 : 64;
   if (esize(q->dtype) <= 2 && q->dim >= 256 && q->dim % 256 == 0) pl.dch = 256;
   const int nch = (q->dim + pl.dch - 1) / pl.dch;
   // the query operand sits in VGPRs when d fits one chunk of at most 128
@@ -243,13 +248,15 @@ constexpr size_t TOPK_LDS = 4096;
 // Untuned keys: eight waves, the shape by what was measured on MI355X (us of a
 // pass: 2 GB of ragged documents scored by one query / 0.5 GB of candidates of
 // eight queries, unless said; Q blocks: 16 query tokens each):
-//   * 64-wide chunks (d above 128, no multiple of it): register-direct, three
-//     steps in flight (FP16 d = 400, two blocks 402 / 179 against 448 / 196
-//     staged);
 //   * FP32: register-direct, two steps (d = 64, four blocks 628 / 226 against
 //     644 / 228); staged for one block without candidates (d = 256 343 against
 //     357); four waves where candidates give a wave at most a document (1,000
 //     of a 64-token query: 60 against 82);
+//   * several 128-wide chunks (d above 128, no multiple of 256) of the narrow
+//     types: register-direct, three steps (FP8 d = 448 285 / 149 against 350 /
+//     193 staged, FP16 with candidates d = 400 165 against 198); FP16 and BF16
+//     staged, two steps, without candidates where rows are whole 128-byte lines
+//     (d = 320 249 against 282; but d = 400 302 against 313);
 //   * eight blocks: staged with two steps for one unit (2.87 against 2.92 ms
 //     over 1M documents), direct for several, whose documents come from the
 //     caches (16 queries, 100K documents: 0.94 against 1.03 ms), and for FP8
@@ -265,17 +272,17 @@ constexpr size_t TOPK_LDS = 4096;
 FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
   const DevInfo di = device_info();
   const int esz = esize(pl.dt);
-  const bool cand = units == 2, chunk64 = pl.dch == 64 && pl.P.nch > 1;
+  const bool cand = units == 2;
   FusedCfg c;
   c.nw = 8;
   c.wg_per_cu = 0;
   if (pl.dt == MAXSIM_F32) {
-    c.pf = chunk64 ? 3 : 2;
-    c.stage = !chunk64 && !cand && pl.nqb == 1;
+    c.pf = 2;
+    c.stage = pl.dch == 128 && !cand && pl.nqb == 1;
     if (cand && pl.n_pairs <= 8 * (int64_t)di.cus) c.nw = 4;
-  } else if (chunk64) {
-    c.pf = 3;
-    c.stage = 0;
+  } else if (pl.dch == 128 && pl.P.nch > 1) {
+    c.stage = esz == 2 && !cand && pl.P.row_bytes % 128 == 0;
+    c.pf = c.stage ? 2 : 3;
   } else if (pl.nqb == 8) {
     c.stage = !units && pl.dt != MAXSIM_F8E4M3;
     c.pf = c.stage ? 2 : 3;

@@ -4,8 +4,9 @@
 // to the whole query (BQ = Nq), so each document byte crosses HBM once
 // (Theorem 1), re-designed for gfx950:
 //   * a document tile is 16 rows x one d-chunk (DCH = 128, the paper's
-//     dimension tiling; 64 when d is not a multiple of 128; 256 for 1- and
-//     2-byte rows of d >= 512, the same k order in longer contiguous reads);
+//     dimension tiling; 64 for d <= 64 and for FP32 where d is not a multiple
+//     of 128; 256 for 1- and 2-byte rows of a d that is a multiple of 256, the
+//     same k order in longer contiguous reads);
 //     lane (r, g) = (lane % 16, lane / 16) consumes row r, bytes
 //     [c*64 + g*16, +16) of the chunk for c < NL as its MFMA A operand, either
 //     loaded straight into VGPRs or staged through a per-wave LDS ring by

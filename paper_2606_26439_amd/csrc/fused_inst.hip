@@ -60,9 +60,10 @@ FusedFns pick_q(int qm, int rt) {
                 occupancy_fused_t<NQB, DCH, PF, NW, fused_detail::Q_SHARED, STAGE>, STAGE};
       return {nullptr, nullptr, STAGE};
     }
-  } else if constexpr (NQB == 8) {
+  } else if constexpr (NQB == 8 || (DCH == 64 && DT != DT_F32)) {
     // eight query blocks only with the query operand in VGPRs, and only for
-    // 1- and 2-byte elements (the host never asks for anything else)
+    // 1- and 2-byte elements; 64-wide chunks of those only for d <= 64, one
+    // chunk (the host never asks for anything else)
     if constexpr (DT == DT_F32) {
       return {nullptr, nullptr, STAGE};
     } else {
