@@ -8,8 +8,8 @@
 // The first term does not depend on the document, so one small MFMA kernel
 // tabulates P[c, (a, t)] = C[c] . q_t of query a for every centroid c (FP32,
 // in the caller's workspace; each query owns QW = 16 * NQB columns, NQB the
-// 16-token blocks of the longest query rounded up to a power of two, zero
-// past its last token). Where the table would cost more than it saves
+// 16-token blocks of the longest query rounded up to a power of two; the
+// blocks that hold its tokens are written, zero past the last one). Where the table would cost more than it saves
 // (maxsim_residual_score's rule), the kernel gathers the centroid itself and
 // adds q_t . C[id] in the same order, so the scores have the same bits. The
 // fused kernel then reads each
@@ -40,7 +40,8 @@
 namespace {
 
 // P[c, a * QW + t] = C[c] . q_t of query a (t < its length), 0 for t up to
-// QW. One wave per 16 centroids and every 16-column block of every query;
+// the end of its last block; later blocks are not read, so not written (eight
+// queries of 8 to 64 tokens, 2^17 centroids: 86 us, 96 with all of them). One wave per 16 centroids and every 16-column block of every query;
 // 4 waves per group.
 template <int NKS>
 __global__ __launch_bounds__(256) void centroid_table_kernel(ResParams P) {
@@ -61,7 +62,9 @@ __global__ __launch_bounds__(256) void centroid_table_kernel(ResParams P) {
     const int64_t qa = blk / bpq;
     const int t = (int)(blk % bpq) * 16 + r;
     const int64_t q0 = sload_i64(P.q_off, qa);
-    const bool live = t < (int)(sload_i64(P.q_off, qa + 1) - q0);
+    const int nq = (int)(sload_i64(P.q_off, qa + 1) - q0);
+    if (blk % bpq > 0 && (int)(blk % bpq) * 16 >= nq) continue;
+    const bool live = t < nq;
     const _Float16* qrow = (const _Float16*)P.q_tok + (live ? q0 + t : 0) * DIM + g * (DIM / 4);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -131,8 +134,27 @@ struct Slot {
   static constexpr int ROWS_OFF = 0, CODES_OFF = 16 * ROW, IDS_OFF = CODES_OFF + 16 * ROWB;
   static constexpr int BYTES = IDS_OFF + 64;
   static constexpr int OPS = 1 + NCI + NG;  // vector memory operations per tile
-  // 16-byte piece p of gathered row rho lies at rho * CPR + (p ^ swz(rho)):
-  // the 16 rows an operand read touches fall in 16 different bank groups
+  // 16-byte piece p of gathered row rho lies at rho * CPR + place(rho, p): the
+  // 16 rows an operand read touches fall in 16 different bank groups (rows of
+  // 12 pieces start at four of the 16 groups: a turn by rho / 4 separates the
+  // rows that start alike)
+  __device__ static int place(int rho, int p) {
+    if constexpr (CPR == 12) {
+      const int q = p + (rho >> 2);
+      return q < CPR ? q : q - CPR;
+    } else {
+      return p ^ swz(rho);
+    }
+  }
+  // the piece that lies at place q
+  __device__ static int piece_at(int rho, int q) {
+    if constexpr (CPR == 12) {
+      const int p = q - (rho >> 2);
+      return p >= 0 ? p : p + CPR;
+    } else {
+      return q ^ swz(rho);
+    }
+  }
   __device__ static int swz(int rho) {
     constexpr int SW = CPR < 16 ? CPR : 16;
     return (rho / (16 / SW)) & (SW - 1);
@@ -275,7 +297,7 @@ __device__ __forceinline__ void score_range(const ResParams& P, int64_t a, int64
       const int piece = w * 64 + lane;
       const int rho = piece / CPR, p = piece % CPR;
       const uint32_t id = ids[w] < max_c ? ids[w] : max_c;
-      load_to_lds<16, false>(gat + (uint64_t)id * stride + (p ^ L::swz(rho)) * 16,
+      load_to_lds<16, false>(gat + (uint64_t)id * stride + L::piece_at(rho, p) * 16,
                              slot + w * 1024);
     }
   };
@@ -404,7 +426,7 @@ __device__ __forceinline__ void score_range(const ResParams& P, int64_t a, int64
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int p = DIRECT ? g * NKS + i : i * 4 + g;
-      rows[i] = *(const u32x4*)(slot + (r * CPR + (p ^ L::swz(r))) * 16);
+      rows[i] = *(const u32x4*)(slot + (r * CPR + L::place(r, p)) * 16);
     }
     read_ids(slot, ids);
   };
@@ -545,6 +567,8 @@ __global__ __launch_bounds__(NW * 64, NQB * NKS <= (DIRECT ? 4 : 8) ? 4 : 2) voi
       score_range<NBITS, NKS, 1, PF, DIRECT>(P, a, base, pb, hi, qa0, nq, poison, lutb, ring);
     } else if (NQB >= 4 && nq <= 32) {
       score_range<NBITS, NKS, 2, PF, DIRECT>(P, a, base, pb, hi, qa0, nq, poison, lutb, ring);
+    } else if (NQB >= 4 && nq <= 48) {
+      score_range<NBITS, NKS, 3, PF, DIRECT>(P, a, base, pb, hi, qa0, nq, poison, lutb, ring);
     } else {
       score_range<NBITS, NKS, NQB, PF, DIRECT>(P, a, base, pb, hi, qa0, nq, poison, lutb, ring);
     }

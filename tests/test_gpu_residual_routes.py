@@ -46,3 +46,21 @@ def test_uneven_candidate_lists_share_a_launch(nq_lens):
     Q, D = _device(c)
     got = M.residual_score(Q, D, M.Candidates(dev(off), dev(ids))).cpu().numpy()
     assert_close_o1(got, _oracle(c, off, ids), f"residual uneven {nq_lens}")
+
+
+@pytest.mark.parametrize("nbits,dim", [(1, 64), (2, 128), (4, 128), (2, 256)])
+def test_each_query_uses_its_own_blocks(nbits, dim):
+    # one to four blocks in one batch, over a table whose unwritten columns
+    # hold NaN: every query's scores are the bits it has alone, on both routes
+    nq = [64, 33, 48, 49, 17, 32, 16, 1] * 2
+    c = _case(310, dim, nbits, 257, seed=dim + nbits, nq_lens=nq)
+    Q, D = _device(c)
+    ws = torch.full((M.residual_workspace_bytes(Q, D),), 255, dtype=torch.uint8, device="cuda")
+    batch = M.residual_score(Q, D, workspace=ws)  # 16 x 21K tokens over 257 centroids: table
+    assert_close_o1(batch.cpu().numpy(), _oracle(c), f"residual blocks {dim} {nbits}")
+    for a in range(8):
+        lo, hi = int(c["q_off"][a]), int(c["q_off"][a + 1])
+        one = M.Tokens(Q.tokens[lo:hi].contiguous(), dev(np.array([0, hi - lo], np.int64)), "f16")
+        cand = M.Candidates(dev(np.array([0, 310], np.int64)), dev(np.arange(310, dtype=np.int32)))
+        alone = M.residual_score(one, D, cand)  # 21K tokens: centroids gathered
+        assert torch.equal(alone, batch[a * 310:(a + 1) * 310]), nq[a]
