@@ -330,17 +330,25 @@ int pow2_at_least(int x) {
 
 // Kernel choice, LDS layout and grid of a fused launch (topk_k > 0: with the
 // top-k epilogue, whose key slots take the LDS the tuned occupancy leaves).
-maxsim_status prepare_fused(const FusedPlan& pl, const FusedCfg& cfg, int topk_k, FusedLaunch& L) {
+maxsim_status prepare_fused(const FusedPlan& pl, FusedCfg cfg, int topk_k, FusedLaunch& L) {
   DevInfo di = device_info();
+  const size_t room = di.max_lds - (topk_k > 0 ? TOPK_LDS : 0);
   // 256-wide chunks exist only with LDS-staged tiles, and only where their
   // ring fits beside one copy of the query blocks; else 128-wide
   FusedParams P = pl.P;
   int dch = pl.dch;
-  if (dch == 256 && (!cfg.stage || pl.lds + (size_t)cfg.nw * cfg.pf * 16 * 256 * esize(pl.dt) +
-                                           (topk_k > 0 ? TOPK_LDS : 0) > di.max_lds)) {
+  if (dch == 256 && (!cfg.stage || pl.lds + (size_t)cfg.nw * cfg.pf * 16 * 256 * esize(pl.dt) >
+                                       room)) {
     dch = 128;  // d is a multiple of 256 here: the same padded row
     P.nch = P.dim / dch;
   }
+  // A saved shape of a narrow type at a d that is no multiple of 128 may come
+  // from a build that staged 64-wide chunks there: where its ring fitted and
+  // the 128-wide one does not, the same waves run register-direct.
+  const int pad64 = (P.dim + 63) / 64 * 64, step = cfg.nw * cfg.pf * 16 * esize(pl.dt);
+  if (cfg.stage && dch == 128 && P.nch > 1 && P.dim % 128 && pl.lds + (size_t)step * 128 > room &&
+      (size_t)pl.nqb * 16 * pad64 * esize(pl.dt) + (size_t)step * 64 <= di.max_lds)
+    cfg.stage = 0;
   // 32-row steps only where they exist (FP8, staged, one chunk)
   const int rt = (cfg.rows == 32 && cfg.stage && pl.qreg && pl.dt == MAXSIM_F8E4M3) ? 32 : 16;
   // query operand: VGPRs when d fits one chunk, else one LDS copy per wave
@@ -351,7 +359,7 @@ maxsim_status prepare_fused(const FusedPlan& pl, const FusedCfg& cfg, int topk_k
   if (pl.qreg) {
     qm = 1;
     lds = ring;
-  } else if ((size_t)cfg.nw * pl.lds + ring <= di.max_lds) {
+  } else if ((size_t)cfg.nw * pl.lds + ring <= room) {
     qm = 2;
     lds = (size_t)cfg.nw * pl.lds + ring;
   } else {
@@ -547,12 +555,14 @@ namespace {
 // pairs) and its workspace layout.
 maxsim_status plan_score_topk(const maxsim_csr* q, const maxsim_csr* d,
                               const maxsim_candidates* cand, int32_t k, FusedPlan& pl,
-                              FusedLaunch& L, TopkLayout& T, bool* overflow = nullptr) {
+                              FusedLaunch& L, TopkLayout& T, bool* overflow = nullptr,
+                              bool few_parts = false) {
   if (k < 1 || k > 1024) return fail(MAXSIM_EINVAL, "score_topk: k=%d must be in [1, 1024]", k);
   maxsim_status st = plan_fused(q, d, cand, nullptr, pl, true, /*need_scores=*/false);
   if (st) return st;
   if (pl.n_pairs > 0) {
     FusedCfg cfg = lookup_cfg(pl, true);
+    if (few_parts) cfg.wg_per_cu = 1;
     if ((st = prepare_fused(pl, cfg, k, L))) return st;
   } else {
     L.P = pl.P;
@@ -684,6 +694,12 @@ maxsim_status maxsim_score_topk_noalloc(const maxsim_csr* queries, const maxsim_
   if (st) return st;
   if (queries->n_sets == 0) return MAXSIM_OK;
   if (!out_scores || !out_ids) return fail(MAXSIM_EINVAL, "score_topk_noalloc: NULL output");
+  if (T.total > (size_t)MAXSIM_NOALLOC_SCRATCH_BYTES) {
+    // one workgroup per compute unit leaves the fewest top-k parts
+    pl = FusedPlan();
+    L = FusedLaunch();
+    if ((st = plan_score_topk(queries, docs, cand, k, pl, L, T, nullptr, true))) return st;
+  }
   if (T.total > (size_t)MAXSIM_NOALLOC_SCRATCH_BYTES)
     return fail(MAXSIM_EWORKSPACE,
                 "score_topk_noalloc: this problem needs %zu bytes of workspace, above the fixed "
