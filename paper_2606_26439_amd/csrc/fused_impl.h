@@ -162,6 +162,23 @@ constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4
 // expcnt at their maxima
 constexpr int lgkmcnt0_imm() { return 0xF | (0x3 << 14) | (0x7 << 4); }
 
+// The queries a0 .. a1 that a workgroup's waves scored candidates of: owners[w]
+// and owners[nw + w] are the queries of wave w's first and last piece, -1 where
+// it scored none (an empty range, or positions that offsets breaking the
+// contract give to no query). False when no wave scored any. Whatever the
+// offsets, 0 <= a0 and a1 < n_q.
+__host__ __device__ inline bool scored_queries(const int64_t* owners, int nw, int64_t n_q,
+                                               int64_t& a0, int64_t& a1) {
+  a0 = a1 = -1;
+  for (int w = 0; w < nw; ++w) {
+    if (owners[w] < 0) continue;
+    if (a0 < 0) a0 = owners[w];
+    a1 = owners[nw + w];
+  }
+  if (a1 >= n_q) a1 = n_q - 1;
+  return a0 >= 0;
+}
+
 // Fused top-k, after every wave of the workgroup has stored its keys: for
 // each query with work pairs in the workgroup's range, the k best ranking keys
 // of those pairs (exact radix select over the workgroup's contiguous key
@@ -169,7 +186,7 @@ constexpr int lgkmcnt0_imm() { return 0xF | (0x3 << 14) | (0x7 << 4); }
 // ranges did not fit them) go to the query's part slot.
 // ranges[w], ranges[NW + w]: first and end work pair of wave w (contiguous);
 // with candidate lists ranges[2 NW + w], ranges[3 NW + w]: the queries of its
-// first and last pair. wg: the workgroup's place in the order of the pairs.
+// first and last pair, or -1. wg: the workgroup's place in the order of the pairs.
 template <int NW>
 __device__ void topk_epilogue(const FusedParams& P, int64_t wg, u32x4* lds, const int64_t* ranges) {
   using namespace topk_detail;
@@ -191,15 +208,7 @@ __device__ void topk_epilogue(const FusedParams& P, int64_t wg, u32x4* lds, cons
     a0 = lo / P.n_docs;
     a1 = (hi - 1) / P.n_docs;
   } else {
-    // the queries of the first and the last wave that had pairs
-    const int64_t* owners = ranges + 2 * NW;
-    a0 = a1 = -1;
-    for (int w = 0; w < NW; ++w) {
-      if (ranges[w] < ranges[NW + w]) {
-        if (a0 < 0) a0 = owners[w];
-        a1 = owners[NW + w];
-      }
-    }
+    if (!scored_queries(ranges + 2 * NW, NW, P.n_q, a0, a1)) return;
   }
   for (int64_t a = a0; a <= a1; ++a) {
     int64_t s0 = lo, s1 = hi;  // (a query alone with the range needs no offsets)
@@ -358,6 +367,8 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     if (lane == 0) {
       ranges[wave] = my_lo;
       ranges[NW + wave] = my_hi;
+      ranges[2 * NW + wave] = -1;
+      ranges[3 * NW + wave] = -1;
     }
     __syncthreads();
     wg_lo = uniform64(ranges[0]);
@@ -421,8 +432,8 @@ __global__ __launch_bounds__(NW * 64) void fused_maxsim_kernel(FusedParams P) {
     int64_t lo = my_lo > pb ? my_lo : pb;
     const int64_t hi = my_hi < se ? my_hi : se;
     if (P.topk_k > 0 && P.cand_off != nullptr && lo < hi && lane == 0) {
-      if (lo == my_lo) ranges[2 * NW + wave] = a;
-      if (hi == my_hi) ranges[3 * NW + wave] = a;
+      if (ranges[2 * NW + wave] < 0) ranges[2 * NW + wave] = a;
+      ranges[3 * NW + wave] = a;
     }
     const int64_t pair_base = (P.cand_off == nullptr) ? a * P.n_docs : 0;
 

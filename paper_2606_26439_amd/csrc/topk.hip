@@ -407,7 +407,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
   // first work pair (for b0, the last workgroup with R(b) <= ps, and b1, the
   // last with R(b) <= pe - 1: R is non-decreasing with R(0) = 0, so each is a
   // count minus one) and the size of its part for this query (0 when it
-  // scored nothing).
+  // scored nothing, and never more than k, whatever a slot that offsets
+  // breaking the contract left unwritten holds).
   if (threadIdx.x < 2) hist[threadIdx.x] = 0u;
   __syncthreads();
   uint32_t c0 = 0, c1 = 0;
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
     const uint32_t c = M.part_cnt[(b + a) * G + gq];
     c0 += r <= ps ? 1u : 0u;
     c1 += r <= pe - 1 ? 1u : 0u;
-    cnts[b] = (uint16_t)(r < r1 ? c : 0u);
+    cnts[b] = (uint16_t)(r < r1 ? (c < (uint32_t)k ? c : (uint32_t)k) : 0u);
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -428,7 +429,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
     atomicAdd(&hist[1], c1);
   }
   __syncthreads();
-  const int64_t b0 = (int64_t)hist[0] - 1, b1 = (int64_t)hist[1] - 1;
+  const int64_t b0 = hist[0] > 0u ? (int64_t)hist[0] - 1 : 0;
+  const int64_t b1 = (int64_t)hist[1] - 1 > b0 ? (int64_t)hist[1] - 1 : b0;
   __syncthreads();
   const int nb = (int)(b1 - b0 + 1);
   auto part = [&](int bi) -> const uint64_t* {
