@@ -273,10 +273,13 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
   vmem_wait<PF - 1>();
   cvec cv = *(const cvec*)(ring + r * M);
   // a step: the next tile's codes out of its slot, this tile's slot refilled
-  // (its codes are in registers), then the arithmetic
+  // (its codes are in registers), then the arithmetic. The wait for LDS reads
+  // is for this tile's codes, read a step ago, which the refill overwrites (it
+  // comes before the next tile's read, so that one is not waited for).
   while (fl[0] & F_VALID) {
 #pragma unroll
     for (int k = 0; k < PF; ++k) {
+      lds_reads_wait();
       vmem_wait<PF - 2>();
       const cvec nx = *(const cvec*)(ring + ((k + 1) % PF) * SLOT + r * M);
       const int f = fl[k];
@@ -285,7 +288,8 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
       cv = nx;
     }
   }
-  // the idle refills still target this wave's ring
+  // the idle refills and the last read still use this wave's ring
+  lds_reads_wait();
   vmem_wait<0>();
   flush(n_out & 63);
 }
