@@ -229,7 +229,11 @@ __device__ __forceinline__ const char* zero_row_ptr() {
 // register allocator's hands; the compiler only counts fewer operations in
 // flight than there are, which makes its own waits stricter, never looser.
 // The memory clobbers keep LDS accesses on their side of each load and wait.
-// The wave's own count is the caller's: lds_wait<N>() returns when at most N
+// The loads take their LDS address from m0, which the compiler reserves and
+// takes on no clobber list. Nothing else in a kernel that uses load_to_lds may
+// use m0 (no LDS-DMA builtin, no indirect register index); a CPU test looks
+// for it in the assembly.
+// The wave's own count is the caller's: vmem_wait<N>() returns when at most N
 // vector memory operations of the wave are in flight (they retire in order).
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
@@ -240,16 +244,16 @@ __device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
   lds = __builtin_amdgcn_readfirstlane(lds);
   if constexpr (B == 16 && NT)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
-                 :: "v"(src), "s"(lds) : "memory", "m0");
+                 :: "v"(src), "s"(lds) : "memory");
   else if constexpr (B == 16)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(src), "s"(lds) : "memory", "m0");
+                 :: "v"(src), "s"(lds) : "memory");
   else if constexpr (NT)
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off nt"
-                 :: "v"(src), "s"(lds) : "memory", "m0");
+                 :: "v"(src), "s"(lds) : "memory");
   else
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-                 :: "v"(src), "s"(lds) : "memory", "m0");
+                 :: "v"(src), "s"(lds) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void vmem_wait() {

@@ -18,6 +18,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # step's load refills slot k + 1; a residual slot is read and refilled in one
 # step.
 RUNS = {"pq_mfma": 1, "residual": 0}
+clobbers = {}
 
 
 @pytest.fixture(scope="module", params=sorted(RUNS))
@@ -30,7 +31,8 @@ def program(request, tmp_path_factory):
     cmd = [HIPCC, "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xclang", "-target-feature",
            "-Xclang", "-packed-fp32-ops", "-fno-honor-nans", "-I", os.path.join(ROOT, "include"),
            "-x", "hip", "--cuda-device-only", "-S", src, "-o", str(out)]
-    subprocess.run(cmd, check=True, capture_output=True)
+    r = subprocess.run(cmd, check=True, capture_output=True, text=True)
+    clobbers[request.param] = [ln for ln in r.stderr.splitlines() if "clobber" in ln]
     ins, labels, inline = [], {}, False
     for ln in out.read_text().splitlines():
         if "#ASMSTART" in ln or "#ASMEND" in ln:
@@ -80,3 +82,12 @@ def test_a_slot_is_refilled_only_after_the_wait_for_its_reads(program):
     assert len(starts) >= 4
     for i in starts:
         assert _unwaited_loads(ins, labels, i) <= RUNS[name], (name, i)
+
+
+def test_m0_belongs_to_the_inline_loads(program):
+    # they set it without saying so to the compiler, which may keep nothing
+    # of its own there
+    name, ins, _ = program
+    assert not clobbers[name]
+    assert not [ln for ln, inline in ins if not inline and re.search(r"\bm0\b", ln)]
+
