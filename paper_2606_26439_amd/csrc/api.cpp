@@ -244,6 +244,8 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
 
 // LDS that a launch with the top-k epilogue keeps for keys and wave ranges.
 constexpr size_t TOPK_LDS = 4096;
+// ... of which each wave's range and owners take
+constexpr size_t topk_ranges_bytes(int nw) { return (size_t)nw * 32; }
 
 // Untuned keys: eight waves, the shape by what was measured on MI355X (us of a
 // pass: 2 GB of ragged documents scored by one query / 0.5 GB of candidates of
@@ -349,6 +351,14 @@ maxsim_status prepare_fused(const FusedPlan& pl, FusedCfg cfg, int topk_k, Fused
   if (cfg.stage && dch == 128 && P.nch > 1 && P.dim % 128 && pl.lds + (size_t)step * 128 > room &&
       (size_t)pl.nqb * 16 * pad64 * esize(pl.dt) + (size_t)step * 64 <= di.max_lds)
     cfg.stage = 0;
+  // A saved shape is timed without the top-k epilogue: where one copy of the
+  // query blocks and the ring leave no room for the epilogue's wave ranges (they
+  // fill the LDS at FP16, d = 768, four blocks, eight waves, two steps), the same
+  // waves run register-direct.
+  if (topk_k > 0 && cfg.stage && !pl.qreg) {
+    const size_t staged = pl.lds + (size_t)step * dch;
+    if (staged <= di.max_lds && staged + topk_ranges_bytes(cfg.nw) > di.max_lds) cfg.stage = 0;
+  }
   // 32-row steps only where they exist (FP8, staged, one chunk)
   const int rt = (cfg.rows == 32 && cfg.stage && pl.qreg && pl.dt == MAXSIM_F8E4M3) ? 32 : 16;
   // query operand: VGPRs when d fits one chunk, else one LDS copy per wave
@@ -382,7 +392,7 @@ maxsim_status prepare_fused(const FusedPlan& pl, FusedCfg cfg, int topk_k, Fused
     P.topk_k = topk_k;
     P.sel_cap = std::min(2048, std::max(256, pow2_at_least(2 * topk_k)));
     const size_t head = (std::max(lds, fused_topk_scratch_bytes(P.sel_cap)) + 15) & ~(size_t)15;
-    const size_t ranges = (size_t)cfg.nw * 32;
+    const size_t ranges = topk_ranges_bytes(cfg.nw);
     const size_t share = di.max_lds / (size_t)per_cu;
     int64_t slots = share > head + ranges ? (int64_t)((share - head - ranges) / 4) : 0;
     slots = std::min<int64_t>(slots, 65536);
