@@ -318,6 +318,15 @@ template <class Cnt, class Part>
 __device__ __forceinline__ void merge_parts(int nb, int k, Cnt cnt, Part part, uint32_t* hist,
                                             uint64_t* gat, uint64_t* buf, float* os, int32_t* oi) {
   using namespace topk_detail;
+  if (nb == 1) {  // the part is the answer (1,000 segments of 50, k = 100: 28 us, 15 this way)
+    const uint64_t* only = part(0);
+    for (int i = threadIdx.x; i < k; i += MERGE_THREADS) {
+      const uint64_t key = (uint32_t)i < cnt(0) ? only[i] : 0ull;
+      os[i] = key == 0ull ? -__builtin_inff() : key_score((uint32_t)(key >> 32));
+      oi[i] = key == 0ull ? -1 : key_id(key);
+    }
+    return;
+  }
   // Fast path: the k best of the first m keys of every part (each part is
   // sorted) are the answer when no part holds a key left out that could reach
   // it, i.e. when every part with more than m keys has its (m+1)-th key below
@@ -460,27 +469,44 @@ namespace {
 
 constexpr int PART_SCORES = 6144;  // score keys of a share kept in LDS
 constexpr int PART_AIM = 2048;     // a share of an average segment
+constexpr int PART_FILL = 512;     // workgroups that fill the device (two of 1,024 threads per CU)
 
-// Parts of a segment in its workspace: np counts, then np times k keys.
+// Parts of a segment in its workspace: np counts, then np times k keys. A
+// share is an np-th of the segment; with GROW it is `least` scores at least, so
+// a segment may use only the first of its parts.
 __device__ __forceinline__ uint32_t* part_counts(void* ws, int64_t s) { return (uint32_t*)seg_ws(ws, s); }
 __device__ __forceinline__ uint64_t* part_keys(void* ws, int64_t s, int np) {
   return (uint64_t*)((char*)seg_ws(ws, s) + (((size_t)np * 4 + 15) & ~(size_t)15));
 }
 int max_parts(int k) { return (int)((seg_ws_bytes() - 16) / ((size_t)k * 8 + 4)); }
 
+template <bool GROW>
 __global__ __launch_bounds__(MERGE_THREADS) void topk_part_kernel(
     const float* __restrict__ scores, const int64_t* __restrict__ seg_off,
-    const int32_t* __restrict__ ids, void* ws, int k, int np) {
+    const int32_t* __restrict__ ids, void* ws, int k, int np, int64_t least,
+    uint32_t n_seg, uint32_t turn) {
   using namespace topk_detail;
   __shared__ uint64_t buf[MERGE_CAP];
   __shared__ uint32_t hist[SEL_HIST_WORDS];
   __shared__ uint32_t sk[PART_SCORES];
-  const int64_t s = blockIdx.y;
-  const int b = blockIdx.x;
+  int64_t s = blockIdx.y;
+  int b = blockIdx.x;
+  if constexpr (GROW) {
+    // Segments along x, so that the parts left empty are the launch's last and
+    // not always the same XCDs' (workgroup i runs on XCD i mod 8: 64 segments of
+    // 100K scores with three parts of eight used took 124 us, 45 this way), and
+    // turned by one for each part where their number is even, so that a long
+    // segment's parts are on all XCDs (99 of 1K and one of 5M: 290 us, 155 with
+    // it). turn: 0 for an odd number, else a mask below n_seg.
+    b = blockIdx.y;
+    uint32_t at = blockIdx.x + ((uint32_t)b & turn);
+    s = at < n_seg ? at : at - n_seg;
+  }
   const int64_t start = seg_off[s], len = seg_off[s + 1] - start;
-  const int64_t share = (len + np - 1) / np;
-  const int64_t lo = share * b < len ? share * b : len;
-  const int64_t n = (len - lo < share ? len - lo : share);
+  int64_t share = (len + np - 1) / np;
+  if constexpr (GROW) share = uniform64(share > least ? share : least);
+  const int64_t lo = share * b;
+  const int64_t n = (len - lo < share ? len - lo : share);  // (<= 0: nothing left for this part)
   const float* sc = scores + start + lo;
   int count = 0;
   if (n > 0) {
@@ -500,6 +526,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_part_kernel(
   if (threadIdx.x == 0) part_counts(ws, s)[b] = (uint32_t)count;
 }
 
+template <bool GROW>
 __global__ __launch_bounds__(MERGE_THREADS) void topk_part_merge_kernel(
     void* ws, int k, int np, float* __restrict__ out_scores, int32_t* __restrict__ out_ids) {
   using namespace topk_detail;
@@ -511,9 +538,18 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_part_merge_kernel(
   const uint32_t* counts = part_counts(ws, s);
   for (int b = threadIdx.x; b < np; b += MERGE_THREADS) cnts[b] = (uint16_t)counts[b];
   __syncthreads();
+  int used = np;
+  if constexpr (GROW) {  // the parts with keys are the first ones
+    used = 0;
+    for (int b0 = 0; b0 < np; b0 += 64) {
+      const int b = b0 + lane_id();
+      used += __popcll(__ballot(b < np && cnts[b] != 0));
+    }
+    used = uniform(used > 1 ? used : 1);
+  }
   const uint64_t* keys = part_keys(ws, s, np);
   merge_parts(
-      np, k, [&](int b) -> uint32_t { return cnts[b]; },
+      used, k, [&](int b) -> uint32_t { return cnts[b]; },
       [&](int b) -> const uint64_t* { return keys + (int64_t)b * k; }, hist, gat, buf,
       out_scores + s * k, out_ids + s * k);
 }
@@ -532,17 +568,35 @@ hipError_t launch_topk(const float* scores, const int64_t* seg_off, int64_t n_se
   const int64_t avg = n_total / n_seg;
   // Shares of about PART_AIM scores (so that a segment three times the average
   // still has its shares in LDS), as many as the workspace has room for the
-  // parts of; where that makes a share longer than four times that
-  // (k = 1000 from about 220K scores a segment on), the histogram launches.
+  // parts of; where that makes a share longer than 4 * PART_SCORES, the
+  // histogram launches (k = 1000 from 221K scores a segment on: eight segments
+  // of 200K 39 us with shares of 22K scores against 86; of 300K 76 us).
   // Eight segments of 1K to 94K scores, k = 100: 32 us against 65.
   const int64_t np =
       std::min<int64_t>(std::max<int64_t>(1, (avg + PART_AIM - 1) / PART_AIM),
                         std::min(max_parts(k), MERGE_MAX_GRID));
   if (avg <= np * PART_SCORES * 4) {
-    hipLaunchKernelGGL(topk_part_kernel, dim3((unsigned)np, (unsigned)n_seg), dim3(MERGE_THREADS),
-                       0, st, scores, seg_off, ids, ws, k, (int)np);
-    hipLaunchKernelGGL(topk_part_merge_kernel, dim3((unsigned)n_seg), dim3(MERGE_THREADS), 0, st,
-                       ws, k, (int)np, out_scores, out_ids);
+    // A selection costs little more for a longer share, so where the parts are
+    // more than twice what the device runs at once, shares grow until it runs
+    // them at once, or to 4 * PART_SCORES. Us for shares of PART_AIM, grown, and
+    // the histogram launches, k = 100: 64 segments of 50K 64, 33, 76; 1,000 of 2,500
+    // 93, 40, 95, of 20K 347, 109, 265. Below that line growing gives less or nothing (256
+    // segments of 5K 33 against 35; 32 of 300K, k = 300, 76 against 83).
+    const int64_t least = std::min<int64_t>(PART_SCORES * 4, n_total / PART_FILL);
+    if (np * n_seg > 2 * PART_FILL) {
+      const uint32_t turn = n_seg % 2 ? 0 : n_seg >= 8 ? 7 : n_seg >= 4 ? 3 : 1;
+      hipLaunchKernelGGL((topk_part_kernel<true>), dim3((unsigned)n_seg, (unsigned)np),
+                         dim3(MERGE_THREADS), 0, st, scores, seg_off, ids, ws, k, (int)np, least,
+                         (uint32_t)n_seg, turn);
+      hipLaunchKernelGGL((topk_part_merge_kernel<true>), dim3((unsigned)n_seg), dim3(MERGE_THREADS),
+                         0, st, ws, k, (int)np, out_scores, out_ids);
+    } else {
+      hipLaunchKernelGGL((topk_part_kernel<false>), dim3((unsigned)np, (unsigned)n_seg),
+                         dim3(MERGE_THREADS), 0, st, scores, seg_off, ids, ws, k, (int)np, (int64_t)0,
+                         0u, 0u);
+      hipLaunchKernelGGL((topk_part_merge_kernel<false>), dim3((unsigned)n_seg),
+                         dim3(MERGE_THREADS), 0, st, ws, k, (int)np, out_scores, out_ids);
+    }
     return hipGetLastError();
   }
   int64_t bps = avg / (TK_THREADS * 16);
