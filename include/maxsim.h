@@ -323,7 +323,7 @@ maxsim_status maxsim_score_topk_noalloc(const maxsim_csr* queries, const maxsim_
  * problem with HIP events (synchronises `stream`), keeps the fastest for the
  * key (dtype, dim, query-token capacity of a unit, and whether the problem is
  * one unit of queries, several, or candidate lists: "units" 0, 1 or 2; an
- * entry without it holds for all), and, if cache_path is not NULL, rewrites
+ * entry without it holds for those of the three that have none with it), and, if cache_path is not NULL, rewrites
  * that JSON file with every tuned key. maxsim_score then uses the tuned
  * configuration for matching keys. Writes a one-line JSON report of the
  * timings to report (if not NULL, up to report_len bytes).

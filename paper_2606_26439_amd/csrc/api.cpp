@@ -94,7 +94,8 @@ DevInfo device_info() {
 // units: 0 when a launch has one query unit, 1 when several units re-read the
 // same documents (those come from the caches then, not from HBM), 2 with
 // candidate lists (scattered documents, often only a few for each wave). A
-// cache entry without it holds for all until one with it says otherwise.
+// cache entry without it is kept as -1 and holds where no entry with it does,
+// whichever was read first.
 struct TuneKey {
   int dt, dim, nqb, units;
   bool operator<(const TuneKey& o) const {
@@ -311,6 +312,7 @@ FusedCfg lookup_cfg(const FusedPlan& pl, bool topk = false) {
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(k);
+    if (it == g_tuned.end()) it = g_tuned.find({k.dt, k.dim, k.nqb, -1});
     if (it != g_tuned.end()) return it->second;
   }
   return default_cfg(pl, k.units, topk);
@@ -472,7 +474,7 @@ std::string cfg_json_all() {
   bool first = true;
   for (auto& kv : g_tuned) {
     char b[224], units[24] = "";
-    if (kv.first.units) snprintf(units, sizeof units, ",\"units\":%d", kv.first.units);
+    if (kv.first.units >= 0) snprintf(units, sizeof units, ",\"units\":%d", kv.first.units);
     snprintf(b, sizeof b,
              "%s{\"dtype\":%d,\"dim\":%d,\"nqb\":%d%s,\"pf\":%d,\"nw\":%d,\"wg_per_cu\":%d,"
              "\"stage\":%d,\"rows\":%d}",
@@ -1441,10 +1443,10 @@ maxsim_status maxsim_load_tune_cache(const char* path) {
       if (!json_int(obj.c_str(), "rows", c.rows)) c.rows = 16;
       if ((c.pf >= 2 && c.pf <= 4) && (c.nw == 4 || c.nw == 8) && (c.stage == 0 || c.stage == 1) &&
           (c.rows == 16 || c.rows == 32)) {
-        int units = -1;  // every value
-        const bool one = json_int(obj.c_str(), "units", units);
-        for (k.units = 0; k.units < 3; ++k.units)
-          if (!one || k.units == units) g_tuned[k] = c;
+        if (!json_int(obj.c_str(), "units", k.units))
+          g_tuned[{k.dt, k.dim, k.nqb, -1}] = c;
+        else if (k.units >= 0 && k.units <= 2)
+          g_tuned[k] = c;
       }
     }
     pos = end;

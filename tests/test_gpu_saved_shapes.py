@@ -47,3 +47,34 @@ def test_a_shape_that_fills_the_lds_serves_top_k_too(dtype, dim, nw, lens, tmp_p
     for cand in (None, M.Candidates(off, ids)):
         ts, ti = M.score_topk(Q, D, 10, cand)
         assert torch.equal(ts, rs) and torch.equal(ti, ri)
+
+
+def _entries(path, dtype, dim):
+    return [e for e in json.loads(path.read_text())["entries"]
+            if e.get("dtype") == _CODE[dtype] and e.get("dim") == dim]
+
+
+def test_the_cache_survives_its_round_trip(tmp_path):
+    # a shape tuned for one query holds for that alone, in the process that
+    # tuned it, in the file, and in a process that reads the file
+    Q, D = _problem("f16", 80, [32])
+    first, second = tmp_path / "a.json", tmp_path / "b.json"
+    M.autotune(Q, D, reps=1, cache_path=str(first))
+    tuned = _entries(first, "f16", 80)
+    assert [e["units"] for e in tuned] == [0]
+    entry = {**tuned[0], "dim": 112}  # as a process that has tuned nothing reads it
+    _load(tmp_path / "c.json", [entry])
+    M.autotune(*_problem("f16", 80, [32]), reps=1, cache_path=str(second))
+    assert _entries(second, "f16", 112) == [entry]
+
+
+@pytest.mark.parametrize("generic_last", [False, True])
+def test_entries_for_a_form_stay_beside_those_for_all(tmp_path, generic_last):
+    dim = 208 + 16 * generic_last
+    base = {"dtype": 2, "dim": dim, "nqb": 2, "pf": 3, "wg_per_cu": 0, "stage": 0, "rows": 16}
+    files = [[{**base, "units": 2, "nw": 8}], [{**base, "nw": 4}]]
+    for i, entries in enumerate(files if generic_last else files[::-1]):
+        _load(tmp_path / f"{i}.json", entries)
+    out = tmp_path / "all.json"
+    M.autotune(*_problem("f16", 80, [32]), reps=1, cache_path=str(out))
+    assert {e.get("units"): e["nw"] for e in _entries(out, "f16", dim)} == {None: 4, 2: 8}
