@@ -150,8 +150,11 @@ struct FusedPlan {
   int64_t n_pairs = 0;
 };
 
+// How far queries are grouped into units that share their document reads.
+enum class Group { none, half_lds, full };
+
 maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_candidates* cand,
-                         float* scores, FusedPlan& pl, bool group_queries = true,
+                         float* scores, FusedPlan& pl, Group grouping = Group::full,
                          bool need_scores = true) {
   maxsim_status st = check_csr(q, "queries", true);
   if (st) return st;
@@ -199,15 +202,16 @@ maxsim_status plan_fused(const maxsim_csr* q, const maxsim_csr* d, const maxsim_
   // the query operand's row in LDS spans whole chunks
   const int qrow_bytes = nch * pl.dch * esize(q->dtype);
   int group = 1;
-  if (!cand && group_queries) {
+  if (!cand && grouping != Group::none) {
     // in LDS (d beyond one chunk) the grouped query blocks take up to four
     // fifths of it: a document read saved is worth more than the staging ring
     // (d = 768, 32-token queries: two at once 1235 -> 834 us over 50K documents
     // of 70 tokens, sixteen 8.56 -> 4.75 ms; d = 1024, four 1895 -> 1145 us).
-    // Only half of it from 2^23 pairs on: a group's top-k parts add up, and
-    // what fits the fixed scratch of maxsim_score_topk_noalloc stays within it.
+    // Half of it from 2^23 pairs on, where four fifths have not been measured,
+    // and where the caller asks for that.
     const int cap = (pl.qreg && esize(q->dtype) <= 2) ? 8 : 4;
-    const size_t lds = device_info().max_lds, room = n_pairs < (1 << 23) ? lds / 5 * 4 : lds / 2;
+    const bool most = grouping == Group::full && n_pairs < (1 << 23);
+    const size_t lds = device_info().max_lds, room = most ? lds / 5 * 4 : lds / 2;
     auto fits = [&](int gr) {
       return pl.qreg || (size_t)gr * bpq * 16 * qrow_bytes <= room;
     };
@@ -568,9 +572,9 @@ namespace {
 maxsim_status plan_score_topk(const maxsim_csr* q, const maxsim_csr* d,
                               const maxsim_candidates* cand, int32_t k, FusedPlan& pl,
                               FusedLaunch& L, TopkLayout& T, bool* overflow = nullptr,
-                              bool few_parts = false) {
+                              bool few_parts = false, Group grouping = Group::full) {
   if (k < 1 || k > 1024) return fail(MAXSIM_EINVAL, "score_topk: k=%d must be in [1, 1024]", k);
-  maxsim_status st = plan_fused(q, d, cand, nullptr, pl, true, /*need_scores=*/false);
+  maxsim_status st = plan_fused(q, d, cand, nullptr, pl, grouping, /*need_scores=*/false);
   if (st) return st;
   if (pl.n_pairs > 0) {
     FusedCfg cfg = lookup_cfg(pl, true);
@@ -706,11 +710,13 @@ maxsim_status maxsim_score_topk_noalloc(const maxsim_csr* queries, const maxsim_
   if (st) return st;
   if (queries->n_sets == 0) return MAXSIM_OK;
   if (!out_scores || !out_ids) return fail(MAXSIM_EINVAL, "score_topk_noalloc: NULL output");
-  if (T.total > (size_t)MAXSIM_NOALLOC_SCRATCH_BYTES) {
-    // one workgroup per compute unit leaves the fewest top-k parts
+  // one workgroup per compute unit leaves fewer top-k parts, and smaller groups
+  // of queries fewer still (each workgroup has a part for every query of a group)
+  for (Group grouping : {Group::full, Group::half_lds}) {
+    if (T.total <= (size_t)MAXSIM_NOALLOC_SCRATCH_BYTES) break;
     pl = FusedPlan();
     L = FusedLaunch();
-    if ((st = plan_score_topk(queries, docs, cand, k, pl, L, T, nullptr, true))) return st;
+    if ((st = plan_score_topk(queries, docs, cand, k, pl, L, T, nullptr, true, grouping))) return st;
   }
   if (T.total > (size_t)MAXSIM_NOALLOC_SCRATCH_BYTES)
     return fail(MAXSIM_EWORKSPACE,
@@ -738,7 +744,7 @@ maxsim_status maxsim_score_unfused(const maxsim_csr* queries, const maxsim_csr* 
                                    float* scores, void* workspace, size_t ws_bytes,
                                    maxsim_stream_t stream) {
   FusedPlan pl;
-  maxsim_status st = plan_fused(queries, docs, nullptr, scores, pl, /*group_queries=*/false);
+  maxsim_status st = plan_fused(queries, docs, nullptr, scores, pl, Group::none);
   if (st) return st;
   if (pl.dch == 256) {  // the comparator's tiles are 128 wide at most (d % 256 == 0 here)
     pl.dch = 128;
