@@ -795,8 +795,8 @@ bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_can
   const int dim = d->M * d->dsub;
   const int bpq = pow2_at_least(std::max(1, (q->max_len + 15) / 16));
   if (bpq * dim > 1024) return false;  // query operand registers
-  if (pq_mfma_lds(d->M, d->K, d->dsub, std::min(8, 1024 / dim), 2) > device_info().max_lds)
-    return false;
+  const size_t books = (size_t)d->M * d->K * d->dsub * 2;
+  if (books > device_info().max_lds) return false;
   // Query blocks per document pass. Eight at d <= 64 (0.50 ms against 0.62
   // with four for 32 queries over 60K documents); four above: at d = 128 they
   // leave four waves per SIMD (64 queries over 250K documents 7.24 against
@@ -817,8 +817,11 @@ bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_can
   P.bpq = bpq;
   P.nqb = nqb;
   P.group = nqb / bpq;
-  // two waves where the codebooks leave no room for eight waves' rings
-  P.nw = pq_mfma_lds(d->M, d->K, d->dsub, nqb, 8) <= device_info().max_lds ? 8 : 2;
+  // codes and scores in registers where the codebooks leave no room for the
+  // waves' rings (M = 16, dsub = 32 from K = 149 or 151 on; 60K documents, one
+  // 32-token query: 146 us at K = 160, 145 with the rings at K = 140)
+  P.nw = 8;
+  P.ring = pq_mfma_lds(d->M, d->K, d->dsub, nqb, P.nw) <= device_info().max_lds ? 1 : 0;
   // (beyond 2^31 items of a query group and at least 64 documents, about eight
   // per CU, the table kernel is asked)
   const int64_t n_groups = std::max<int64_t>(1, (q->n_sets + P.group - 1) / P.group);
@@ -831,7 +834,7 @@ bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_can
   // a wave's span of positions is counted in 32 bits: a pool near that size
   // is shared out by documents, not by tokens
   if (d->n_docs >= 0x7fffffffLL - 64) P.tokens_per_query = 0;
-  pl.lds = pq_mfma_lds(d->M, d->K, d->dsub, nqb, P.nw);
+  pl.lds = P.ring ? pq_mfma_lds(d->M, d->K, d->dsub, nqb, P.nw) : books;
   pl.ws = 0;
   pl.variant = 1;
   return true;

@@ -123,17 +123,20 @@ struct PqParams {
   int32_t qt;        // query tokens per slice (LUT rows)
   int32_t n_slices;  // ceil(max Nq / qt)
   int32_t n_chunks;  // doc-range chunks per (query, slice) or per query group
-  int32_t nw;        // waves per workgroup (8 or 16; decode-into-MFMA 8 or 2)
+  int32_t nw;        // waves per workgroup (8 or 16; decode-into-MFMA 8)
   // decode-into-MFMA variant only
   int32_t bpq;    // 16-column query blocks per query (ceil(max Nq / 16))
   int32_t group;  // queries per work item
   int32_t nqb;    // query blocks per wave (group * bpq)
   int32_t cus;    // compute units of the device
+  int32_t ring;   // 1: codes and scores pass through LDS beside the codebooks
+  int32_t pad;
 };
 hipError_t launch_pq(const PqParams& P, int max_nq, hipStream_t s);
 // Decode-into-MFMA PQ scorer: F16 queries and codebooks, dsub in {8, 16, 32};
 // nqb in {1, 2, 4, 8} with nqb * M * dsub <= 1024; lds from pq_mfma_lds():
-// the codebooks, then per wave four tiles of codes and 64 scores of each block.
+// the codebooks, then (ring) per wave four tiles of codes and 64 scores of each
+// block.
 constexpr int PQ_RING = 4;  // code tiles in flight per wave
 constexpr int pq_mfma_wave_lds(int M, int nqb) { return PQ_RING * 16 * M + nqb * 256; }
 constexpr size_t pq_mfma_lds(int M, int K, int dsub, int nqb, int nw) {

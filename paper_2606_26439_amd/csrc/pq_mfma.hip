@@ -59,8 +59,10 @@ constexpr int PF = PQ_RING;
 
 // One wave's scores: positions [lo, hi) (position base + b is document b, or
 // position p is candidate p) of the gsz queries from a0 on, whose tokens fill
-// NB blocks of 16 columns, bpq of them per query.
-template <int M, int DSUB, int NB>
+// NB blocks of 16 columns, bpq of them per query. RING: codes and scores pass
+// through this wave's LDS (ring, sc); else, where the codebooks leave none, they
+// stay in registers.
+template <int M, int DSUB, int NB, bool RING>
 __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int gsz, int bpq,
                                             int64_t base, int64_t lo, int64_t hi,
                                             const char* cbl, char* ring, float* sc,
@@ -156,8 +158,9 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
   // each, four bytes per lane), so their loads hold no registers and nothing
   // but this wave's own counted waits waits for them. Every refill issues one
   // load (from the zero row when there is nothing left).
-  const uint32_t ring_at = lds_offset(ring);
+  const uint32_t ring_at = RING ? lds_offset(ring) : 0u;
   const int crow = lane * 4 / M, ccol = lane * 4 % M;
+  cvec code_reg[RING ? 1 : PF];
   auto refill = [&](int k) -> int {
     const char* src = zrow;
     int f = 0, lim = 0;
@@ -173,8 +176,12 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
         f = F_VALID | (last ? F_DLAST : 0);
       }
     }
-    if (4 * M >= 64 || lane < 4 * M)
-      load_to_lds<4, false>(src + (crow < lim ? crow : lim) * M + ccol, ring_at + k * SLOT);
+    if constexpr (RING) {
+      if (4 * M >= 64 || lane < 4 * M)
+        load_to_lds<4, false>(src + (crow < lim ? crow : lim) * M + ccol, ring_at + k * SLOT);
+    } else {
+      code_reg[k] = *(const cvec*)(src + (r < lim ? r : lim) * M);
+    }
     if (last) {
       ++cp;
       enter_doc();
@@ -184,12 +191,18 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
     return f;
   };
 
-  // 64 documents' scores are kept in LDS, a row of 64 for the query whose last
-  // block is nb, and written a row at a time
+  // 64 documents' scores are kept in LDS (or one per lane), a row of 64 for the
+  // query whose last block is nb, and written a row at a time
   float* const out = P.scores + lo + (has_cand ? 0 : (a0 - base / P.n_docs) * P.n_docs);
   int n_out = 0;  // documents scored
+  float sc_reg[RING ? 1 : NB];
   auto put = [&](int nb, float v) {
-    if (lane == 0) sc[nb * 64 + (n_out & 63)] = v;
+    if constexpr (RING) {
+      if (lane == 0) sc[nb * 64 + (n_out & 63)] = v;
+    } else {
+      v = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+      sc_reg[nb] = lane == (n_out & 63) ? v : sc_reg[nb];
+    }
   };
   auto flush = [&](int n) {
 #pragma unroll
@@ -199,8 +212,12 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
         if (((valid_m >> gq) & 1u) && lane < n) {
           // query longer than its bound: NaN (as a bit pattern; this file
           // assumes no NaN arithmetic)
-          const float v =
-              ((poison_m >> gq) & 1u) ? __builtin_bit_cast(float, 0x7fc00000u) : sc[nb * 64 + lane];
+          float v;
+          if constexpr (RING)
+            v = sc[nb * 64 + lane];
+          else
+            v = sc_reg[nb];
+          if ((poison_m >> gq) & 1u) v = __builtin_bit_cast(float, 0x7fc00000u);
           out[(int64_t)gq * P.n_docs + n_out - n + lane] = v;
         }
       }
@@ -214,6 +231,8 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
   float mx[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) mx[nb] = -__builtin_inff();
+  if constexpr (!RING)
+    for (int nb = 0; nb < NB; ++nb) sc_reg[nb] = 0.f;
 
   auto consume = [&](const cvec& cv, int fl) {
     if (!(fl & F_VALID)) return;
@@ -270,27 +289,39 @@ __device__ __forceinline__ void score_range(const PqParams& P, int64_t a0, int g
   int fl[PF];
 #pragma unroll
   for (int k = 0; k < PF; ++k) fl[k] = refill(k);
-  vmem_wait<PF - 1>();
-  cvec cv = *(const cvec*)(ring + r * M);
-  // a step: the next tile's codes out of its slot, this tile's slot refilled
-  // (its codes are in registers), then the arithmetic. The wait for LDS reads
-  // is for this tile's codes, read a step ago, which the refill overwrites (it
-  // comes before the next tile's read, so that one is not waited for).
-  while (fl[0] & F_VALID) {
+  if constexpr (RING) {
+    vmem_wait<PF - 1>();
+    cvec cv = *(const cvec*)(ring + r * M);
+    // a step: the next tile's codes out of its slot, this tile's slot refilled
+    // (its codes are in registers), then the arithmetic. The wait for LDS reads
+    // is for this tile's codes, read a step ago, which the refill overwrites (it
+    // comes before the next tile's read, so that one is not waited for).
+    while (fl[0] & F_VALID) {
 #pragma unroll
-    for (int k = 0; k < PF; ++k) {
-      lds_reads_wait();
-      vmem_wait<PF - 2>();
-      const cvec nx = *(const cvec*)(ring + ((k + 1) % PF) * SLOT + r * M);
-      const int f = fl[k];
-      fl[k] = refill(k);
-      consume(cv, f);
-      cv = nx;
+      for (int k = 0; k < PF; ++k) {
+        lds_reads_wait();
+        vmem_wait<PF - 2>();
+        const cvec nx = *(const cvec*)(ring + ((k + 1) % PF) * SLOT + r * M);
+        const int f = fl[k];
+        fl[k] = refill(k);
+        consume(cv, f);
+        cv = nx;
+      }
+    }
+    // the idle refills and the last read still use this wave's ring
+    lds_reads_wait();
+    vmem_wait<0>();
+  } else {
+    while (fl[0] & F_VALID) {
+#pragma unroll
+      for (int k = 0; k < PF; ++k) {
+        const cvec cv = code_reg[k];
+        const int f = fl[k];
+        fl[k] = refill(k);
+        consume(cv, f);
+      }
     }
   }
-  // the idle refills and the last read still use this wave's ring
-  lds_reads_wait();
-  vmem_wait<0>();
   flush(n_out & 63);
 }
 
@@ -306,8 +337,10 @@ __device__ int64_t pq_range_begin(const PqParams& P, int64_t w, int64_t W, int64
   return u * P.n_docs + wave_lower_bound(P.d_off, P.n_docs, tau - u * T);
 }
 
-template <int M, int DSUB, int NQB, int NW>
-__global__ __launch_bounds__(NW * 64, NQB * M * DSUB <= 512 ? 4 : 2) void pq_mfma_kernel(PqParams P) {
+constexpr int NW = 8;  // waves per workgroup
+
+template <int M, int DSUB, int NQB, bool RING>
+__global__ __launch_bounds__(NW * 64, RING && NQB * M * DSUB <= 512 ? 4 : 2) void pq_mfma_kernel(PqParams P) {
   extern __shared__ u32x4 cb_lds[];  // codebooks [M][K][DSUB] FP16
   // ---- codebooks into LDS (16-byte copies) ----
   {
@@ -323,7 +356,7 @@ __global__ __launch_bounds__(NW * 64, NQB * M * DSUB <= 512 ? 4 : 2) void pq_mfm
   const int64_t pe = uniform64(pq_range_begin(P, w + 1, W, n));
   __syncthreads();
   const char* cbl = (const char*)cb_lds;
-  char* ring = (char*)cb_lds + M * P.K * DSUB * 2 +
+  char* ring = (char*)cb_lds + M * P.K * DSUB * 2 +  // (only with RING)
                uniform(threadIdx.x >> 6) * pq_mfma_wave_lds(M, NQB);
   float* sc = (float*)(ring + PF * 16 * M);
   const char* const zrow = zero_row_ptr();
@@ -356,20 +389,20 @@ __global__ __launch_bounds__(NW * 64, NQB * M * DSUB <= 512 ? 4 : 2) void pq_mfm
       own = nq <= 16 ? 1 : (nq + 15) / 16;
     }
     if (NQB > 1 && NQB <= 4 && own == 1)
-      score_range<M, DSUB, 1>(P, a0, gsz, 1, base, pb, hi, cbl, ring, sc, zrow);
+      score_range<M, DSUB, 1, RING>(P, a0, gsz, 1, base, pb, hi, cbl, ring, sc, zrow);
     else if (NQB > 2 && NQB <= 4 && own == 2)
-      score_range<M, DSUB, 2>(P, a0, gsz, 2, base, pb, hi, cbl, ring, sc, zrow);
+      score_range<M, DSUB, 2, RING>(P, a0, gsz, 2, base, pb, hi, cbl, ring, sc, zrow);
     else if (NQB > 3 && NQB <= 4 && own == 3)
-      score_range<M, DSUB, 3>(P, a0, gsz, 3, base, pb, hi, cbl, ring, sc, zrow);
+      score_range<M, DSUB, 3, RING>(P, a0, gsz, 3, base, pb, hi, cbl, ring, sc, zrow);
     else
-      score_range<M, DSUB, NQB>(P, a0, gsz, P.bpq, base, pb, hi, cbl, ring, sc, zrow);
+      score_range<M, DSUB, NQB, RING>(P, a0, gsz, P.bpq, base, pb, hi, cbl, ring, sc, zrow);
     pb = hi;
   }
 }
 
-template <int M, int DSUB, int NQB, int NW>
-hipError_t launch_mfma_w(const PqParams& P, size_t lds, hipStream_t s) {
-  auto k = pq_mfma_kernel<M, DSUB, NQB, NW>;
+template <int M, int DSUB, int NQB, bool RING>
+hipError_t launch_mfma_r(const PqParams& P, size_t lds, hipStream_t s) {
+  auto k = pq_mfma_kernel<M, DSUB, NQB, RING>;
   if (lds > 64 * 1024) {
     hipError_t e =
         hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -397,11 +430,11 @@ hipError_t launch_mfma_w(const PqParams& P, size_t lds, hipStream_t s) {
 
 template <int M, int DSUB, int NQB>
 hipError_t launch_mfma_t(const PqParams& P, size_t lds, hipStream_t s) {
-  // two waves: only codebooks near the size of the LDS (M * dsub = 512)
+  // no ring: only codebooks near the size of the LDS (M * dsub = 512)
   if constexpr (M * DSUB >= 512) {
-    if (P.nw == 2) return launch_mfma_w<M, DSUB, NQB, 2>(P, lds, s);
+    if (!P.ring) return launch_mfma_r<M, DSUB, NQB, false>(P, lds, s);
   }
-  return launch_mfma_w<M, DSUB, NQB, 8>(P, lds, s);
+  return launch_mfma_r<M, DSUB, NQB, true>(P, lds, s);
 }
 
 template <int M, int DSUB>
