@@ -785,6 +785,13 @@ PqCfg lookup_pq(const PqKey& k) {
   return it == g_pq_tuned.end() ? PqCfg{} : it->second;
 }
 
+// The PQ decode and residual scorers share positions (document of a query, or
+// candidate) out to at least nw waves on every compute unit, and a wave counts
+// its own in 32 bits.
+bool wave_span_fits(int64_t positions, int nw) {
+  return positions / (nw * (int64_t)device_info().cus) < 0x7fffffffLL - 64;
+}
+
 // Decode-into-MFMA plan; returns false when the problem is outside what that
 // kernel handles (the table kernel is used then).
 bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_candidates* cand,
@@ -822,14 +829,8 @@ bool plan_pq_mfma(const maxsim_csr* q, const maxsim_pq_docs* d, const maxsim_can
   // 32-token query: 146 us at K = 160, 145 with the rings at K = 140)
   P.nw = 8;
   P.ring = pq_mfma_lds(d->M, d->K, d->dsub, nqb, P.nw) <= device_info().max_lds ? 1 : 0;
-  // (beyond 2^31 items of a query group and at least 64 documents, about eight
-  // per CU, the table kernel is asked)
-  const int64_t n_groups = std::max<int64_t>(1, (q->n_sets + P.group - 1) / P.group);
-  const int64_t per_group_docs =
-      cand ? (q->n_sets > 0 ? cand->n_total / q->n_sets : 0) : d->n_docs;
-  int64_t n_chunks = ((int64_t)device_info().cus * 8 + n_groups - 1) / n_groups;
-  n_chunks = std::min<int64_t>(n_chunks, std::max<int64_t>(1, per_group_docs / 64));
-  if (n_chunks * n_groups > 0x7fffffffLL) return false;
+  const int64_t n_groups = (q->n_sets + P.group - 1) / P.group;
+  if (!wave_span_fits(cand ? cand->n_total : n_groups * d->n_docs, P.nw)) return false;
   P.cus = device_info().cus;
   // a wave's span of positions is counted in 32 bits: a pool near that size
   // is shared out by documents, not by tokens
@@ -1120,18 +1121,8 @@ maxsim_status plan_residual(const maxsim_csr* q, const maxsim_residual_docs* d,
   P.dim = d->dim;
   P.nbits = d->nbits;
   P.nqb = pow2_at_least(std::max(1, (q->max_len + 15) / 16));
-  // limits: below 2^31 work items of a query and at least 64 documents (about
-  // eight per CU over the batch), each spanning less than 2^31 documents or
-  // candidate positions; a wave of the scorer never spans more than an item
-  const int64_t per_query = cand ? (q->n_sets > 0 ? cand->n_total / q->n_sets : 0) : d->n_docs;
-  const int64_t want = (int64_t)device_info().cus * 8;
-  const int64_t nq = std::max<int64_t>(1, q->n_sets);
-  int64_t n_chunks = std::max<int64_t>(1, (want + nq - 1) / nq);
-  n_chunks = std::min<int64_t>(n_chunks, std::max<int64_t>(1, per_query / 64));
-  if (n_chunks * nq > 0x7fffffffLL) return fail(MAXSIM_EUNSUPPORTED, "residual: too many work items");
-  const int64_t span_bound = (cand ? cand->n_total : d->n_docs) / n_chunks + 1;
-  if (span_bound >= 0x7fffffffLL - 64)
-    return fail(MAXSIM_EUNSUPPORTED, "residual: too many documents per work item");
+  if (!wave_span_fits(n_pairs, 4))
+    return fail(MAXSIM_EUNSUPPORTED, "residual: too many documents for one launch");
   P.cus = device_info().cus;
   P.n_pairs = n_pairs;
   // a wave's span of positions is counted in 32 bits: a pool near that size
