@@ -1047,9 +1047,13 @@ constexpr int RES_DEFAULT_PIPE = 3;
 // Whether the scorer gathers the centroids themselves (2 * dim bytes a token)
 // instead of rows of a centroid-query table (64 bytes a token and block of 16
 // query tokens) that has to be built first. Measured, the scorer takes about
-// 0.094 ps per gathered byte, and the table is built at 3.3 TB/s (centroids
-// read, table written) after a launch worth 13 MB at that rate, so in bytes of
-// the build: direct when 0.31 * tokens * (2 * dim - 64 * blocks) is below it.
+// 0.094 ps per gathered byte and, where it multiplies the centroids itself,
+// 0.012 ps per element and block; the table is built at 3.3 TB/s (centroids
+// read, table written) after a launch worth 13 MB at that rate. So in bytes of
+// the build: direct when 0.31 * tokens * (2 * dim - 64 * blocks + dim * blocks / 8)
+// is below it. (Measured ps a token, table / direct, 2^17 centroids, 2 bits, one
+// query of 16, 32, 48, 64 tokens: d = 64 14 / 18, 18 / 19; d = 128 18 / 36,
+// 22 / 38, 36 / 39, 38 / 46; d = 256 22 / 78, 30 / 79, 45 / 85, 50 / 93.)
 // On either side of the line, 2^17 centroids, one 32-token query, d = 128:
 // 3,000 candidates 21 us direct against 34 us, 30,000 candidates 96 against
 // 74 us. Both forms give the same bits.
@@ -1062,7 +1066,7 @@ bool residual_direct(const ResParams& P, const maxsim_csr* q, const maxsim_resid
   const double blocks = std::min<double>(P.nqb, std::max(1.0, std::ceil(mean_len / 16)));
   const double build =
       13e6 + (double)d->n_centroids * (2.0 * d->dim + 4.0 * (double)P.n_cols);
-  return 0.31 * tokens * (2.0 * d->dim - 64.0 * blocks) < build;
+  return 0.31 * tokens * (2.0 * d->dim - 64.0 * blocks + d->dim * blocks / 8.0) < build;
 }
 
 maxsim_status plan_residual(const maxsim_csr* q, const maxsim_residual_docs* d,

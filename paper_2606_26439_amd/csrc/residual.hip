@@ -161,6 +161,25 @@ struct Slot {
   }
 };
 
+// Whether a wave holds two tiles' operands, so that one's come out of LDS while
+// the other's are contracted. At d = 256 the query operand of three and four
+// blocks takes 96 and 128 registers and two tiles of the table's route no longer
+// fit beside it (100K documents, one 64-token query, 2 bits, 2^12 centroids: 851
+// us with what spilled, 333 with one tile); with two blocks one tile leaves
+// three waves per SIMD instead of two (223 against 208 us).
+constexpr bool two_tiles(int nb, int nks, bool direct) {
+  return direct || (nb * nks < 24 && !(nb == 2 && nks == 8));
+}
+// Waves per SIMD that the registers are shared out for. Gathered centroids at
+// d = 256 with four blocks: one, as the rings leave room for (2^17 centroids,
+// 20,000 candidates of a 64-token query: 860 us with two and what spilled, 206);
+// the table's four blocks at d = 64: two (2^17 centroids, 90,000 candidates of a
+// 64-token query: 643 us with four and what spilled, 261).
+constexpr int waves_per_simd(int nqb, int nks, bool direct) {
+  if (direct) return nqb * nks <= 4 ? 4 : nqb * nks >= 32 ? 1 : 2;
+  return nqb == 4 ? 2 : nqb * nks <= 8 ? 4 : nqb * nks == 16 ? 3 : 2;
+}
+
 // One wave's scores: work positions [lo, hi) of query a (position base + b is
 // document b, or position p is candidate p), NB blocks of 16 query tokens.
 //
@@ -459,42 +478,61 @@ __device__ __forceinline__ void score_range(const ResParams& P, int64_t a, int64
     ahead[k] = next_tile();
     issue_ids(ahead[k], slot);
   };
-  u32x4 res[NKS], rows[NR];
-  int fl = now[0].flags;
-  {
-    uint32_t ids[L::NG];
-    ResWords<RB> rw;
-    vmem_wait<(PF - 1) * L::OPS>();
-    take_raw(ring, rows, ids, rw);
-    decode(rw, res);
-    refill(0, ids);
-  }
-  // Whole rounds of PF steps. A step's arithmetic runs on operands taken a
-  // step earlier, while the next tile's come out of LDS (the codes, then the
-  // byte-table reads they address), so a wave waits for neither; the table
-  // reads come before the step's refill, because after it the compiler would
-  // wait for every load in flight. The tiles after a wave's last one carry no
-  // flags: their steps compute on what idle refills left and store nothing.
-  while (fl & F_VALID) {
-#pragma unroll
-    for (int k = 0; k < PF; ++k) {
-      const int kn = (k + 1) % PF;
-      // the other slots' loads are younger; slot kn's have landed
-      vmem_wait<(PF - 1) * L::OPS>();
-      u32x4 res2[NKS], rows2[NR];
+  if constexpr (two_tiles(NB, NKS, DIRECT)) {
+    u32x4 res[NKS], rows[NR];
+    int fl = now[0].flags;
+    {
       uint32_t ids[L::NG];
       ResWords<RB> rw;
-      f32x4 acc[NB];
-      take_raw(ring + kn * L::BYTES, rows2, ids, rw);
-      contract(res, rows, acc);
-      decode(rw, res2);
-      finish(fl, acc);
-      fl = now[kn].flags;
-      refill(kn, ids);
+      vmem_wait<(PF - 1) * L::OPS>();
+      take_raw(ring, rows, ids, rw);
+      decode(rw, res);
+      refill(0, ids);
+    }
+    // Whole rounds of PF steps. A step's arithmetic runs on operands taken a
+    // step earlier, while the next tile's come out of LDS (the codes, then the
+    // byte-table reads they address), so a wave waits for neither; the table
+    // reads come before the step's refill, because after it the compiler would
+    // wait for every load in flight. The tiles after a wave's last one carry no
+    // flags: their steps compute on what idle refills left and store nothing.
+    while (fl & F_VALID) {
 #pragma unroll
-      for (int s = 0; s < NKS; ++s) res[s] = res2[s];
+      for (int k = 0; k < PF; ++k) {
+        const int kn = (k + 1) % PF;
+        // the other slots' loads are younger; slot kn's have landed
+        vmem_wait<(PF - 1) * L::OPS>();
+        u32x4 res2[NKS], rows2[NR];
+        uint32_t ids[L::NG];
+        ResWords<RB> rw;
+        f32x4 acc[NB];
+        take_raw(ring + kn * L::BYTES, rows2, ids, rw);
+        contract(res, rows, acc);
+        decode(rw, res2);
+        finish(fl, acc);
+        fl = now[kn].flags;
+        refill(kn, ids);
 #pragma unroll
-      for (int i = 0; i < NR; ++i) rows[i] = rows2[i];
+        for (int s = 0; s < NKS; ++s) res[s] = res2[s];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) rows[i] = rows2[i];
+      }
+    }
+  } else {
+    while (now[0].flags & F_VALID) {
+#pragma unroll
+      for (int k = 0; k < PF; ++k) {
+        vmem_wait<(PF - 1) * L::OPS>();
+        u32x4 res[NKS], rows[NR];
+        uint32_t ids[L::NG];
+        ResWords<RB> rw;
+        f32x4 acc[NB];
+        take_raw(ring + k * L::BYTES, rows, ids, rw);
+        decode(rw, res);
+        const int fl = now[k].flags;
+        refill(k, ids);
+        contract(res, rows, acc);
+        finish(fl, acc);
+      }
     }
   }
   // the idle refills still target this wave's ring
@@ -521,7 +559,7 @@ __device__ int64_t res_range_begin(const ResParams& P, int64_t w, int64_t W) {
 }
 
 template <int NBITS, int NKS, int NQB, int NW, int PF, bool DIRECT>
-__global__ __launch_bounds__(NW * 64, NQB * NKS <= (DIRECT ? 4 : 8) ? 4 : 2) void residual_maxsim_kernel(ResParams P) {
+__global__ __launch_bounds__(NW * 64, waves_per_simd(NQB, NKS, DIRECT)) void residual_maxsim_kernel(ResParams P) {
   constexpr int FPB = 8 / NBITS;
   __shared__ __attribute__((aligned(16))) _Float16 lut[256 * FPB];
   extern __shared__ u32x4 res_lds[];  // the waves' rings
@@ -587,15 +625,17 @@ hipError_t launch_table_t(const ResParams& P, hipStream_t s) {
 template <int NBITS, int NKS, int NQB, bool DIRECT>
 hipError_t launch_score_p(const ResParams& P, hipStream_t s) {
   constexpr int NW = 4;
-  // four tiles in flight per wave (two and three measured slower), or three
-  // where the widest gathered rows leave no room for four
-  constexpr int PF = 512 * (8 / NBITS) + NW * wave_ring_bytes<NBITS, NKS, NQB, 4, DIRECT>() <=
-                             160 * 1024
-                         ? 4
-                         : 3;
+  // Four tiles in flight per wave (two and three measured slower), or three
+  // where that lets two workgroups share a compute unit (100K documents, one
+  // 64-token query, d = 128, 4 bits: 423 -> 306 us) or where the widest gathered
+  // rows leave no room for four.
+  constexpr size_t lut = 512 * (8 / NBITS), unit = 160 * 1024;
+  constexpr size_t four = lut + NW * wave_ring_bytes<NBITS, NKS, NQB, 4, DIRECT>();
+  constexpr size_t three = lut + NW * wave_ring_bytes<NBITS, NKS, NQB, 3, DIRECT>();
+  constexpr int PF = four > unit || (four > unit / 2 && three <= unit / 2) ? 3 : 4;
   auto k = residual_maxsim_kernel<NBITS, NKS, NQB, NW, PF, DIRECT>;
   constexpr size_t lds = NW * wave_ring_bytes<NBITS, NKS, NQB, PF, DIRECT>();
-  static_assert(512 * (8 / NBITS) + lds <= 160 * 1024, "the rings fit the LDS");
+  static_assert(lut + lds <= unit, "the rings fit the LDS");
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
