@@ -255,10 +255,17 @@ constexpr size_t topk_ranges_bytes(int nw) { return (size_t)nw * 32; }
 // Untuned keys: eight waves, the shape by what was measured on MI355X (us of a
 // pass: 2 GB of ragged documents scored by one query / 0.5 GB of candidates of
 // eight queries, unless said; Q blocks: 16 query tokens each):
-//   * FP32: register-direct, two steps (d = 64, four blocks 628 / 226 against
-//     644 / 228); staged for one block without candidates (d = 256 343 against
-//     357); four waves where candidates give a wave at most a document (1,000
-//     of a 64-token query: 60 against 82);
+//   * FP32: register-direct, two steps, for one unit one workgroup per CU
+//     (two 16-token blocks, d = 512, 2,790 documents 147 against 169 with as many
+//     as fit, 20K 573 against 579; d = 256, 4,000 documents 83 against 99); staged
+//     for one block without candidates (d = 256 343 against 357), and with four
+//     waves for four blocks of d <= 64 (30K documents of d = 64: one 64-token query
+//     184 against 191, 24 of 14 tokens 917 against 1023); four waves where
+//     candidates give a wave of eight at most two documents (1,000 of a 64-token
+//     query: 60 against 82; 3,000 111 against 121, 8,000 of d = 64 86 against 84).
+//     At a d above 128 that is no multiple of it, three steps, staged
+//     where there are no candidates, have measured up to 5% faster than these two
+//     (d = 192, one query 317 against 333);
 //   * several 128-wide chunks (d above 128, no multiple of 256) of the narrow
 //     types: register-direct, three steps (FP8 d = 448 285 / 149 against 350 /
 //     193 staged, FP16 with candidates d = 400 165 against 198); FP16 and BF16
@@ -285,8 +292,10 @@ FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
   c.wg_per_cu = 0;
   if (pl.dt == MAXSIM_F32) {
     c.pf = 2;
-    c.stage = pl.dch == 128 && !cand && pl.nqb == 1;
-    if (cand && pl.n_pairs <= 8 * (int64_t)di.cus) c.nw = 4;
+    c.stage = !cand && ((pl.dch == 128 && pl.nqb == 1) || (pl.P.dim <= 64 && pl.nqb == 4));
+    if (c.stage && pl.nqb == 4) c.nw = 4;
+    if (!units && !c.stage) c.wg_per_cu = 1;
+    if (cand && pl.n_pairs <= 16 * (int64_t)di.cus) c.nw = 4;
   } else if (pl.dch == 128 && pl.P.nch > 1) {
     c.stage = esz == 2 && !cand && pl.P.row_bytes % 128 == 0;
     c.pf = c.stage ? 2 : 3;
