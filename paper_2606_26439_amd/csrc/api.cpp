@@ -275,9 +275,14 @@ constexpr size_t topk_ranges_bytes(int nw) { return (size_t)nw * 32; }
 //     over 1M documents), direct for several, whose documents come from the
 //     caches (16 queries, 100K documents: 0.94 against 1.03 ms), and for FP8
 //     (four queries 109 against 130);
-//   * FP8: staged, three steps (d = 256, two blocks 326 against 359 direct);
-//     direct with candidates (four blocks 149 against 183) and at d <= 64 with
-//     four blocks (409 against 427);
+//   * FP8: staged, three steps (d = 256, two blocks 326 against 359 direct; 100K
+//     documents of d = 64 85 against 96); direct at d <= 64 with four blocks (409
+//     against 427), and where a row is shorter than 64 bytes (119K documents of
+//     d = 48, 10 tokens 90 against 98). Candidates: direct while their tokens come
+//     to less than 200 MB, which the last-level cache holds (a 32-token query over
+//     1M documents, d = 128, new lists each time: 10K candidates 26 against 27, 30K
+//     60 against 57; eight queries with 100K each 1374 against 1146); four blocks in
+//     LDS staged with two steps (d = 256, 3,000 candidates 26 against 37);
 //   * FP16 and BF16: staged, two steps (d = 256, four blocks 323 against 356
 //     direct, 405 with four waves); direct where four blocks in LDS meet
 //     candidates (d = 256 140 against 169) or several units (16 queries,
@@ -304,8 +309,15 @@ FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
     c.pf = c.stage ? 2 : 3;
     c.wg_per_cu = 2;
   } else if (pl.dt == MAXSIM_F8E4M3) {
-    c.pf = 3;
-    c.stage = !cand && !(pl.nqb == 4 && pl.dch == 64);
+    const bool wide4 = !pl.qreg && pl.nqb == 4;
+    c.pf = cand && wide4 ? 2 : 3;
+    if (cand) {
+      const double docs = (double)std::max<int64_t>(1, pl.P.n_docs);
+      const double bytes = (double)pl.n_pairs * pl.P.tokens_per_query / docs * pl.P.row_bytes;
+      c.stage = wide4 || bytes >= 200e6;
+    } else {
+      c.stage = !(pl.nqb == 4 && pl.dch == 64) && pl.P.row_bytes >= 64;
+    }
   } else {
     c.stage = pl.qreg || pl.nqb < 4 || !units;
     c.pf = c.stage || cand ? 2 : 4;
