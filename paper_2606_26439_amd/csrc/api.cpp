@@ -282,16 +282,22 @@ constexpr size_t topk_ranges_bytes(int nw) { return (size_t)nw * 32; }
 //     to less than 200 MB, which the last-level cache holds (a 32-token query over
 //     1M documents, d = 128, new lists each time: 10K candidates 26 against 27, 30K
 //     60 against 57; eight queries with 100K each 1374 against 1146); four blocks in
-//     LDS staged with two steps (d = 256, 3,000 candidates 26 against 37);
+//     LDS staged with two steps (d = 256, 3,000 candidates 26 against 37), fewer of
+//     them with few candidates staged with four waves (300 of a 32-token query 17
+//     against 19);
 //   * FP16 and BF16: staged, two steps (d = 256, four blocks 323 against 356
 //     direct, 405 with four waves); direct where four blocks in LDS meet
 //     candidates (d = 256 140 against 169) or several units (16 queries,
-//     d = 768: 4.75 against 5.21 ms);
+//     d = 768: 4.75 against 5.21 ms); few candidates of one block in LDS with four
+//     waves, three steps (four queries with 100 each, d = 768 28 against 32);
 //   * direct wherever the ring does not fit beside the query blocks.
 FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
   const DevInfo di = device_info();
   const int esz = esize(pl.dt);
   const bool cand = units == 2;
+  // candidates of wide rows (query blocks in LDS) that come to at most two
+  // documents for a wave of eight on every CU
+  const bool few = cand && !pl.qreg && pl.n_pairs <= 16 * (int64_t)di.cus;
   FusedCfg c;
   c.nw = 8;
   c.wg_per_cu = 0;
@@ -314,13 +320,18 @@ FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
     if (cand) {
       const double docs = (double)std::max<int64_t>(1, pl.P.n_docs);
       const double bytes = (double)pl.n_pairs * pl.P.tokens_per_query / docs * pl.P.row_bytes;
-      c.stage = wide4 || bytes >= 200e6;
+      c.stage = wide4 || few || bytes >= 200e6;
+      if (few && !wide4) c.nw = 4;
     } else {
       c.stage = !(pl.nqb == 4 && pl.dch == 64) && pl.P.row_bytes >= 64;
     }
   } else {
     c.stage = pl.qreg || pl.nqb < 4 || !units;
     c.pf = c.stage || cand ? 2 : 4;
+    if (few && pl.nqb == 1) {
+      c.nw = 4;
+      c.pf = 3;
+    }
   }
   // (a 256-wide chunk is taken as two of 128 where only their ring fits)
   const size_t q_lds = (pl.qreg ? 0 : pl.lds) + (topk ? TOPK_LDS : 0);
