@@ -25,9 +25,9 @@
 //     v_mfma_scale_f32_16x16x128_f8f6f4 (doc row scale on A, query token
 //     scale on B), which is exact for powers of two;
 //   * the running max of query token n (= lane % 16 of block nb) is in-lane
-//     over the 4 accumulator rows; at a document's end two xor-shuffles finish
-//     the max over rows and four more sum a query's tokens; one lane stores
-//     the score (no atomics, fixed order: bit-reproducible);
+//     over the 4 accumulator rows; at a document's end two lane-row swaps finish
+//     the max over rows and four DPP rotations sum a query's tokens; one lane
+//     stores the score (no atomics, fixed order: bit-reproducible);
 //   * without candidate lists, queries are grouped into units whose blocks
 //     share every tile read (one document read for several queries);
 //   * persistent grid: the (unit, doc) work list is cut into token-balanced

@@ -11,8 +11,8 @@
 // the query tokens held in VGPRs (B operand), several queries per wave, so
 // one decode serves NQB x 16 query tokens. Running maxima stay in VGPRs; rows
 // past a document's end are clamped to its last token; at the document's
-// end two xor-shuffles finish the max over rows and four sum a query's
-// tokens. FP16 products are exact and accumulate in FP32.
+// end two lane-row swaps finish the max over rows and four DPP rotations sum
+// a query's tokens. FP16 products are exact and accumulate in FP32.
 //
 // A work position is (query group, document), or a candidate; every wave takes
 // an equal share of them (document tokens, or candidates). Without candidate

@@ -18,7 +18,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # step's load refills slot k + 1; a residual slot is read and refilled in one
 # step.
 RUNS = {"pq_mfma": 1, "residual": 0}
-clobbers = {}
+clobbers, scratch = {}, {}
 
 
 @pytest.fixture(scope="module", params=sorted(RUNS))
@@ -34,6 +34,8 @@ def program(request, tmp_path_factory):
     r = subprocess.run(cmd, check=True, capture_output=True, text=True)
     clobbers[request.param] = [ln for ln in r.stderr.splitlines() if "clobber" in ln]
     ins, labels, inline = [], {}, False
+    scratch[request.param] = [int(n) for n in re.findall(r"^; ScratchSize: (\d+)", out.read_text(),
+                                                         re.M)]
     for ln in out.read_text().splitlines():
         if "#ASMSTART" in ln or "#ASMEND" in ln:
             inline = "#ASMSTART" in ln
@@ -91,3 +93,10 @@ def test_m0_belongs_to_the_inline_loads(program):
     assert not clobbers[name]
     assert not [ln for ln, inline in ins if not inline and re.search(r"\bm0\b", ln)]
 
+
+
+def test_few_registers_spill(program):
+    # a spilled operand of the inner loop comes back from memory for every tile
+    # (residual, d = 256, 64 tokens: 2.5 to 6 times the time with 172 to 324 bytes)
+    sizes = scratch[program[0]]
+    assert len(sizes) >= 16 and max(sizes) <= 128
