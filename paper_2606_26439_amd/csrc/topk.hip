@@ -400,30 +400,36 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
   const bool dense = M.cand_off == nullptr;
   const int64_t a = dense ? qa / G : qa;
   const int gq = dense ? (int)(qa % G) : 0;
-  const int64_t ps = dense ? a * M.n_docs : M.cand_off[qa];
+  // (not below 0, whatever the offsets: R(0) <= ps, so 0 <= b0 <= b1 below
+  // when anything was scored)
+  int64_t ps = dense ? a * M.n_docs : M.cand_off[qa];
+  ps = ps > 0 ? ps : 0;
   const int64_t pe = dense ? ps + M.n_docs : M.cand_off[qa + 1];
   float* os = M.out_scores + qa * k;
   int32_t* oi = M.out_ids + qa * k;
-  if (ps >= pe) {
+  if (ps >= pe || M.grid == 0) {
     for (int i = threadIdx.x; i < k; i += MERGE_THREADS) {
       os[i] = -__builtin_inff();
       oi[i] = -1;
     }
     return;
   }
-  auto R = [&](int64_t b) -> int64_t { return b >= M.grid ? M.n_upairs : M.wg_lo[b]; };
   // One round of loads for every workgroup b of the scoring launch: its
-  // first work pair (for b0, the last workgroup with R(b) <= ps, and b1, the
-  // last with R(b) <= pe - 1: R is non-decreasing with R(0) = 0, so each is a
-  // count minus one) and the size of its part for this query (0 when it
+  // first work pair R(b) (for b0, the last workgroup with R(b) <= ps, and b1,
+  // the last with R(b) <= pe - 1: R is non-decreasing with R(0) = 0, so each is
+  // a count minus one) and the size of its part for this query (0 when it
   // scored nothing, and never more than k, whatever a slot that offsets
   // breaking the contract left unwritten holds).
   if (threadIdx.x < 2) hist[threadIdx.x] = 0u;
   __syncthreads();
   uint32_t c0 = 0, c1 = 0;
   for (int b = threadIdx.x; b < M.grid; b += MERGE_THREADS) {
-    const int64_t r = R(b), r1 = R(b + 1);
-    const uint32_t c = M.part_cnt[(b + a) * G + gq];
+    int64_t r = M.wg_lo[b], r1 = M.wg_lo[b + 1 < M.grid ? b + 1 : b];
+    uint32_t c = M.part_cnt[(b + a) * G + gq];
+    // (all three in flight before the first is looked at: the compiler would
+    // load c only where r < r1, a round trip later, 0.6 us)
+    asm volatile("" : "+v"(r), "+v"(r1), "+v"(c));
+    if (b + 1 >= M.grid) r1 = M.n_upairs;
     c0 += r <= ps ? 1u : 0u;
     c1 += r <= pe - 1 ? 1u : 0u;
     cnts[b] = (uint16_t)(r < r1 ? (c < (uint32_t)k ? c : (uint32_t)k) : 0u);
@@ -438,8 +444,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void topk_merge_kernel(MergeParams M
     atomicAdd(&hist[1], c1);
   }
   __syncthreads();
-  const int64_t b0 = hist[0] > 0u ? (int64_t)hist[0] - 1 : 0;
-  const int64_t b1 = (int64_t)hist[1] - 1 > b0 ? (int64_t)hist[1] - 1 : b0;
+  const int64_t b0 = (int64_t)hist[0] - 1, b1 = (int64_t)hist[1] - 1;
   __syncthreads();
   const int nb = (int)(b1 - b0 + 1);
   auto part = [&](int bi) -> const uint64_t* {
