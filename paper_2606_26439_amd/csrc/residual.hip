@@ -187,16 +187,16 @@ constexpr int waves_per_simd(int nqb, int nks, bool direct) {
 // per wave: the ids PF tiles ahead of the gathers they address, those and the
 // codes PF tiles ahead of the arithmetic. A gather instruction's consecutive
 // lanes take consecutive 16-byte pieces of one row, so four lanes share one
-// 64-byte access of the vector cache: 41 accesses a tile instead of 143, and
-// the address path 50% busy instead of 81%.
-// Bound (1M documents, one 32-token query, 2 bits, d = 128): with a table the
-// L2s hold (2^12 centroids) LDS, address path and VALU are each half busy and
-// a launch takes 1.15 ms (1.38 before); with 2^17 centroids (16.8 MB against 4
-// MB of L2 per XCD) three quarters of the gathered lines come over the fabric,
-// 10 GB with the streams, and a launch takes 1.34 ms (1.44 before). A batch of
-// eight queries of 8 to 64 tokens with 1K to 100K candidates, table and
-// top-k included: 1.00 ms (1.83 before; most of it the queries' equal shares of
-// workgroups whatever their lists' lengths, and 64 columns for each of them).
+// 64-byte access of the vector cache: 41 accesses a tile instead of 143.
+// Bound (1M documents, one 32-token query, 2 bits, d = 128): the vector cache's
+// address path. It is 78% busy with a table that the L2s hold (2^12 centroids;
+// LDS 53%, half of that conflicts, VALU 56%), a launch of 1.15 ms (1.38 with the
+// gathers in registers), and 87% busy with 2^17 centroids (16.8 MB against 4 MB
+// of L2 per XCD: three quarters of the gathered lines come over the fabric, 10 GB
+// with the streams), 1.32 ms (1.44). A batch of eight queries of 8 to 64 tokens
+// with 1K to 100K candidates, table and top-k included: 0.97 ms (1.83 before;
+// most of it the queries' equal shares of workgroups whatever their lists'
+// lengths, and 64 columns for each of them).
 template <int NBITS, int NKS, int NB, int PF, bool DIRECT>
 __device__ __forceinline__ void score_range(const ResParams& P, int64_t a, int64_t base,
                                             int64_t lo, int64_t hi, int64_t qa0, int nq, bool poison, const char* lutb,
