@@ -281,10 +281,18 @@ constexpr size_t topk_ranges_bytes(int nw) { return (size_t)nw * 32; }
 //     d = 48, 10 tokens 90 against 98). Candidates: direct while their tokens come
 //     to less than 200 MB, which the last-level cache holds (a 32-token query over
 //     1M documents, d = 128, new lists each time: 10K candidates 26 against 27, 30K
-//     60 against 57; eight queries with 100K each 1374 against 1146); four blocks in
-//     LDS staged with two steps (d = 256, 3,000 candidates 26 against 37), fewer of
-//     them with few candidates staged with four waves (300 of a 32-token query 17
-//     against 19);
+//     60 against 57; eight queries with 100K each 1374 against 1146). With the query
+//     blocks in LDS one query's are always staged (d = 768, new lists: 2,000 of a
+//     16-token query 36 against 44, 30K of a 32-token one 311 against 327), four
+//     blocks with two steps (d = 256, 3,000 candidates 26 against 37). Several
+//     queries' are staged from 200 MB too (d = 256, 12 of 32 tokens with 5,000
+//     each 201 against 222), but only where each wave has a copy of the blocks of
+//     its own: the waves of a workgroup that share one take the queries that meet
+//     in it one after the other (d = 512, the same 594 against 419; 8 or 32 equal
+//     lists end where a workgroup does and are 10% faster staged all the same, but
+//     the host knows no list's length). A document a wave or fewer of two
+//     blocks: four staged waves (d = 768, eight lists of 100 43 against 52; one
+//     block 37 against 34);
 //   * FP16 and BF16: staged, two steps (d = 256, four blocks 323 against 356
 //     direct, 405 with four waves); direct where four blocks in LDS meet
 //     candidates (d = 256 140 against 169) or several units (16 queries,
@@ -295,9 +303,9 @@ FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
   const DevInfo di = device_info();
   const int esz = esize(pl.dt);
   const bool cand = units == 2;
-  // candidates of wide rows (query blocks in LDS) that come to at most two
-  // documents for a wave of eight on every CU
-  const bool few = cand && !pl.qreg && pl.n_pairs <= 16 * (int64_t)di.cus;
+  // candidates of wide rows (query blocks in LDS) that come to at most a
+  // document for a wave of four on every CU
+  const bool few = cand && !pl.qreg && pl.n_pairs <= 4 * (int64_t)di.cus;
   FusedCfg c;
   c.nw = 8;
   c.wg_per_cu = 0;
@@ -315,13 +323,16 @@ FusedCfg default_cfg(const FusedPlan& pl, int units, bool topk) {
     c.pf = c.stage ? 2 : 3;
     c.wg_per_cu = 2;
   } else if (pl.dt == MAXSIM_F8E4M3) {
-    const bool wide4 = !pl.qreg && pl.nqb == 4;
-    c.pf = cand && wide4 ? 2 : 3;
+    const bool wide4 = !pl.qreg && pl.nqb == 4, one = pl.P.n_units == 1;
+    c.pf = cand && wide4 && one ? 2 : 3;
     if (cand) {
       const double docs = (double)std::max<int64_t>(1, pl.P.n_docs);
       const double bytes = (double)pl.n_pairs * pl.P.tokens_per_query / docs * pl.P.row_bytes;
-      c.stage = wide4 || few || bytes >= 200e6;
-      if (few && !wide4) c.nw = 4;
+      const size_t wave = pl.lds + (size_t)c.pf * 16 * pl.dch * esz;  // its copy and its ring
+      const size_t room = di.max_lds - (topk ? TOPK_LDS : 0);
+      if (few && !one && pl.nqb == 2 && 4 * wave <= room) c.nw = 4;
+      const bool shared = !pl.qreg && c.nw * wave > room;
+      c.stage = one ? !pl.qreg || bytes >= 200e6 : !shared && (c.nw == 4 || bytes >= 200e6);
     } else {
       c.stage = !(pl.nqb == 4 && pl.dch == 64) && pl.P.row_bytes >= 64;
     }
